@@ -179,26 +179,15 @@ __device__ __forceinline__ Cx cadd(Cx a, Cx b) { return {a.re + b.re, a.im + b.i
 // Results are written once and never read back by the kernel that writes
 // them.  Streaming (nontemporal) stores pass them on towards memory at once
 // instead of leaving them dirty in L2, where the write-back at the end of the
-// kernel would only start after the last workgroup has finished.
+// kernel would only start after the last workgroup has finished.  They also
+// leave the 256 MB memory-side cache to the inputs: with plain stores for P
+// and Q (which let L2 join the two halves of a line that neighbouring tiles
+// share) 100k buses x 32 states took 45.4 us on inputs last used two calls
+// ago, with streaming stores 34.2 us (34.2 and 33.6 us on the inputs of the
+// call before); whole-line row stores gained nothing over either.
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void st_out(double *p, double v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void st_out2(dvec2 *p, dvec2 v) { __builtin_nontemporal_store(v, p); }
-
-// A row output (P, Q or an adjoint gradient) of the packed tiles: a plain
-// store with PLAIN, else a streaming one.  The row ranges of neighbouring
-// tiles share the 128-byte lines at their ends.  When a launch has few
-// state chunks per tile, those tiles write the shared lines at about the
-// same time: plain stores let L2 join the two parts of each line before it
-// goes to memory, where streaming stores write two partial lines.  With
-// many chunks per tile the lines would wait in L2 too long, and streaming
-// stores are faster.
-template <bool PLAIN>
-__device__ __forceinline__ void st_row(double *p, double v) {
-    if constexpr (PLAIN)
-        *p = v;
-    else
-        __builtin_nontemporal_store(v, p);
-}
 
 // Copy a staged tile of J rows (LDS, slot capacity NS) to global memory
 // with 16-byte stores.
@@ -406,7 +395,7 @@ __device__ __forceinline__ EwRow ew_row(double vi, double dA, double dC, double 
 // column-major order (WITH_J only) with the same tiles and staging, each
 // record's slot filled by ew_record_csc and the diagonal entries
 // dQ_i/dtheta_i and dP_i/dv_i trading places.
-template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC, bool PLAIN>
+template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC>
 __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
@@ -703,8 +692,8 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
             }
         }
         if (P && rowt) {
-            st_row<PLAIN>(P + (size_t)s * nb + ir, o.p);
-            st_row<PLAIN>(Q + (size_t)s * nb + ir, o.q);
+            st_out(P + (size_t)s * nb + ir, o.p);
+            st_out(Q + (size_t)s * nb + ir, o.q);
         }
         if constexpr (WITH_J) {
             lds_barrier();
@@ -714,15 +703,15 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
     pipelined_states<In, ONE>(sb, se, first, load, proc);
 }
 
-// PLAIN: plain stores for the rows of P and Q (see st_row).  The
-// injections of several states per workgroup are held to 80 registers
+// The injections of several states per workgroup are held to 80 registers
 // (their natural count is a few above), so that six waves fit per SIMD
-// instead of five.
-template <int NT, bool PAR, bool WITH_J, bool ONE, bool PLAIN = false>
+// instead of five.  The last parameter has one value; it keeps the kernel's
+// name as profiles record it.
+template <int NT, bool PAR, bool WITH_J, bool ONE, bool>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((!ONE && !WITH_J) ? 6 : 1, 8)))
     k_ew(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
          double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, WITH_J, ONE, false, PLAIN>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
+    ew_eval<NT, PAR, WITH_J, ONE, false>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
 }
 
 // Injections and J values in CSC order.
@@ -730,7 +719,7 @@ template <int NT, bool PAR, bool ONE>
 __global__ void __launch_bounds__(NT)
     k_ew_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
              const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, true, ONE, true, false>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
+    ew_eval<NT, PAR, true, ONE, true>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
 }
 
 // ===================================================================
@@ -1092,8 +1081,7 @@ __device__ __forceinline__ double vjp_own(double sum, double vi, double lpi, dou
     return fma(2.0 * vi, fma(lpi, dA, -(lqi * dC)), sum);
 }
 
-// PLAIN: plain stores for the gradient rows (see st_row).
-template <int NT, bool ONE, bool PLAIN = false>
+template <int NT, bool ONE>
 __global__ void __launch_bounds__(NT)
     k_ew_vjp(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
              const double *__restrict__ va, const double *__restrict__ lp, const double *__restrict__ lq,
@@ -1252,8 +1240,8 @@ __global__ void __launch_bounds__(NT)
         const double gm = vjp_own(v, in.vr, in.lpr, in.lqr, dA, dC);
         if (rowt) {
             const size_t so = (size_t)s * nb;
-            st_row<PLAIN>(gva + so + ir, a);
-            st_row<PLAIN>(gvm + so + ir, gm);
+            st_out(gva + so + ir, a);
+            st_out(gvm + so + ir, gm);
         }
     };
     put_own(0, first);
@@ -1706,30 +1694,21 @@ hipError_t launch_nt(const DevGrid &g, const Launch &L, hipStream_t st) {
                                                  : (ntl * nchunk + kXcds - 1) / kXcds * kXcds;
     if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks), block(NT);
-    // Plain row stores for the injections and the adjoint when a tile has at
-    // most eight state chunks (see st_row).
-    const bool plain = !ONE && nchunk <= 8;
     switch (L.kind) {
         case K_EW_S:
-            if (L.has_parallel && plain)
-                hipLaunchKernelGGL((k_ew<NT, true, false, ONE, !ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
-                                   L.vm, L.va, L.p, L.q, nullptr);
-            else if (L.has_parallel)
-                hipLaunchKernelGGL((k_ew<NT, true, false, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
-                                   L.p, L.q, nullptr);
-            else if (plain)
-                hipLaunchKernelGGL((k_ew<NT, false, false, ONE, !ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
+            if (L.has_parallel)
+                hipLaunchKernelGGL((k_ew<NT, true, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
                                    L.vm, L.va, L.p, L.q, nullptr);
             else
-                hipLaunchKernelGGL((k_ew<NT, false, false, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
-                                   L.p, L.q, nullptr);
+                hipLaunchKernelGGL((k_ew<NT, false, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
+                                   L.vm, L.va, L.p, L.q, nullptr);
             break;
         case K_EW_SJ:
             if (L.has_parallel)
-                hipLaunchKernelGGL((k_ew<NT, true, true, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
+                hipLaunchKernelGGL((k_ew<NT, true, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
                                    L.p, L.q, L.jval);
             else
-                hipLaunchKernelGGL((k_ew<NT, false, true, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
+                hipLaunchKernelGGL((k_ew<NT, false, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
                                    L.p, L.q, L.jval);
             break;
         case K_EW_SJ_CSC:
@@ -1745,12 +1724,8 @@ hipError_t launch_nt(const DevGrid &g, const Launch &L, hipStream_t st) {
         case K_YB_SJ_CSC:
             return launch_ybus<NT, ONE>(g, L, grid, block, spb, nchunk, st);
         case K_EW_VJP:
-            if (plain)
-                hipLaunchKernelGGL((k_ew_vjp<NT, ONE, !ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
-                                   L.lp, L.lq, L.gvm, L.gva);
-            else
-                hipLaunchKernelGGL((k_ew_vjp<NT, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va, L.lp,
-                                   L.lq, L.gvm, L.gva);
+            hipLaunchKernelGGL((k_ew_vjp<NT, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va, L.lp,
+                               L.lq, L.gvm, L.gva);
             break;
         default:
             return hipErrorInvalidValue;
@@ -1765,12 +1740,12 @@ int occupancy_nt(int kind, bool par) {
     auto q = [&](const void *f) { e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, NT, 0); };
     switch (kind) {
         case K_EW_S:
-            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, false, ONE>)
-                  : reinterpret_cast<const void *>(&k_ew<NT, false, false, ONE>));
+            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, false, ONE, false>)
+                  : reinterpret_cast<const void *>(&k_ew<NT, false, false, ONE, false>));
             break;
         case K_EW_SJ:
-            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, true, ONE>)
-                  : reinterpret_cast<const void *>(&k_ew<NT, false, true, ONE>));
+            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, true, ONE, false>)
+                  : reinterpret_cast<const void *>(&k_ew<NT, false, true, ONE, false>));
             break;
         case K_EW_SJ_CSC:
             q(par ? reinterpret_cast<const void *>(&k_ew_csc<NT, true, ONE>)
