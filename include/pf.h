@@ -312,11 +312,10 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     of the tiles and walks them chunk by chunk: the tiles'
  *                     tables stay in its L2 while neighbouring workgroups
  *                     write neighbouring parts of J) or PF_ORDER_AUTO
- *                     (Jacobian launches: state-major while the tile tables
- *                     fit in 2 MB, which then stay in every XCD's L2,
- *                     grouped above that; injections and the adjoint:
- *                     tile-major, so the state chunks of one tile share
- *                     an L2)
+ *                     (Jacobian launches: grouped, state-major when the
+ *                     tile tables are below 512 KB; injections and the
+ *                     adjoint: tile-major, so the state chunks of one tile
+ *                     share an L2)
  * The initial schedule is tile_items 256 (with several grids per handle:
  * the smallest of 64, 128, 256 that holds the mean branch ends per grid,
  * since tiles never span grids), states_per_block 0, PF_ORDER_AUTO.

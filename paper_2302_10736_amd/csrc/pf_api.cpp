@@ -918,11 +918,12 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 }
 
 // Work order of a launch (pf::WO_*).  Automatic: for Jacobian launches
-// state-major while the tables fit in one XCD's L2 (2 MB of its 4 MB), so
-// the tiles of a state write neighbouring parts of J together, else grouped
-// (each XCD walks its own eighth of the tiles state by state: their tables
-// stay in its L2 while neighbouring workgroups still write neighbouring J
-// rows); tile-major for injections and the adjoint (the state chunks of one
+// grouped (each XCD walks its own eighth of the tiles state by state: their
+// tables stay in its L2 while neighbouring workgroups write neighbouring J
+// rows, and later states can be read ahead, see ahead_of); state-major for
+// grids of tables below 512 KB, whose eighth would be fewer than eight tiles
+// (2,383 buses x 250 states, Ybus: 20.4 us state-major, 21.0 grouped);
+// tile-major for injections and the adjoint (the state chunks of one
 // tile run on one XCD, so its tables come from that XCD's L2 after the
 // first chunk).
 int work_order(const pf_grid *g, int kind) {
@@ -935,7 +936,8 @@ int work_order(const pf_grid *g, int kind) {
             return pf::WO_GROUPED;
         default:
             if (!is_jacobian(kind)) return pf::WO_TILE;
-            return table_bytes(g, kind) <= ((int64_t)2 << 20) ? pf::WO_STATE : pf::WO_GROUPED;
+            if (table_bytes(g, kind) >= (int64_t)1 << 19) return pf::WO_GROUPED;
+            return pf::WO_STATE;
     }
 }
 
@@ -977,6 +979,23 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     return std::min(fill, 8);
 }
 
+// Read-ahead of a launch (read_ahead in pf_kernels.hip): bursts of 8 states,
+// for Jacobian launches of one state per workgroup in the grouped order.
+// Measured on 20k buses x 512 states with the inputs in HBM: no read-ahead
+// 385 us, bursts of 4 states 334, of 8 308, of 16 314-324, of 32 326.  The
+// distance covers the states that one round of workgroups (7 or 8 on each of
+// an XCD's 32 compute units) has in flight.  The states read ahead have to
+// stay in the XCD's L2 until they are used: 3 of its 4 MB.
+int ahead_of(const pf_grid *g, const pf::Launch &L) {
+    if (!is_jacobian(L.kind) || L.phasor != pf::PH_FLY || L.states_per_block != 1 || L.order != pf::WO_GROUPED) return 0;
+    const bool yb = L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
+    const int64_t walk = ((int64_t)(yb ? g->ytiles : g->tiles).size() + 7) / 8;  // tiles per XCD and state
+    const int64_t burst = 8, dist = 256 / walk + 1;
+    if (L.nstate < dist + burst || walk < 8) return 0;  // fewer states: nothing to gain (40k buses x 8: 1 % lost)
+    if ((burst + dist) * 2 * (int64_t)g->nb > (int64_t)3 << 20) return 0;  // 16 bytes a bus, an eighth of the buses
+    return (int)(burst | dist << 8);
+}
+
 // The two-phase baseline with the given scratch (ten doubles per record).
 int run_two_phase(const pf_grid *g, int32_t nstate, const double *vm, const double *va, double *p, double *q,
                   double *jval, bool pre, double *scr, void *stream) {
@@ -998,6 +1017,7 @@ int run(const pf_grid *g, pf::Launch &L, void *stream) {
     L.has_parallel = g->has_parallel;
     L.states_per_block = auto_states_per_block(g, L.kind, L.nstate);
     L.order = work_order(g, L.kind);
+    L.ahead = ahead_of(g, L);
     if (L.nstate == 0) return PF_OK;
     int cur = -1;
     hipError_t e = hipGetDevice(&cur);

@@ -144,6 +144,7 @@ struct Launch {
     int tile_items;        // workgroup size = records per tile
     int states_per_block;
     int order;             // WO_*
+    int ahead;             // states read ahead (read_ahead in pf_kernels.hip): burst | dist << 8, 0 none
     int nstate;
     bool has_parallel;
     const double *vm, *va, *lp, *lq;

@@ -166,6 +166,49 @@ constexpr int kJStage = 4 * NS + 4;
 __device__ __forceinline__ int lo16(int v) { return v & 0xffff; }
 __device__ __forceinline__ int hi16(int v) { return (int)((unsigned)v >> 16); }
 
+constexpr int kRsrcFlags = 0x00027000;  // raw buffer descriptor, 32-bit data
+
+// Read-ahead of later states in the grouped order, one state per workgroup.
+// A compute unit's L1 serves loads and stores in order, so while a load that
+// misses to HBM is outstanding the unit's J stores wait behind it.  With every
+// workgroup loading its own cold state some miss is always outstanding, and
+// the launch runs at 3.4 TB/s however far ahead the loads are issued.  So the
+// misses are taken in bursts: the workgroups of every `burst`-th state, when
+// their own work is done, read one word of each 128-byte line of their rows'
+// states s + dist .. s + dist + burst - 1 into the XCD's L2 (state 0's also
+// the states before those), and the workgroups in between find their states
+// there.  `ahead` holds burst (a power of two) and dist << 8, or 0 for none.
+// Same tile, later states: the neighbours' rows come from the neighbouring
+// tiles' workgroups, which the grouped order keeps on the same XCD.
+struct Ahead {
+    unsigned v, t;  // words read ahead, never used
+};
+
+template <int NT>
+__device__ __forceinline__ Ahead read_ahead(const Tile &c, size_t nb, int ahead, int s, int nstate, const double *vm,
+                                            const double *va) {
+    const int burst = ahead & 0xff, dist = ahead >> 8;
+    const bool on = burst != 0 && (s & (burst - 1)) == 0;
+    const int first = s == 0 ? 1 : s + dist;
+    const int lines = (c.nrows + 15) / 16 + 1;  // a row range of any alignment
+    const int lg = 32 - __builtin_clz(lines - 1);
+    const int n = on ? min(min(s + dist + burst, nstate) - first, NT >> lg) : 0;
+    // Branch-free, so that the waits for the workgroup's own gathers stay
+    // exact: the descriptor is empty when there is nothing to read, and lanes
+    // without a line lie past its end.
+    const int bytes = n > 0 ? 8 * ((n - 1) * (int)nb + c.nrows) : 0;
+    const int k = NT - 1 - threadIdx.x;  // the waves that hold no rows first
+    const int line = k & ((1 << lg) - 1), u = k >> lg;
+    const int off = u < n ? 8 * (u * (int)nb + min(16 * line, c.nrows - 1)) : -8;
+    const size_t at = (size_t)first * nb + c.r0;
+    const auto rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(vm + at), 0, bytes, kRsrcFlags);
+    const auto rt = __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(va + at), 0, bytes, kRsrcFlags);
+    return {__builtin_amdgcn_raw_buffer_load_b32(rv, off, 0, 0), __builtin_amdgcn_raw_buffer_load_b32(rt, off, 0, 0)};
+}
+
+// The end of a read-ahead: the loads have to have a use.
+__device__ __forceinline__ void ahead_done(const Ahead &a) { asm volatile("" ::"v"(a.v), "v"(a.t)); }
+
 struct Cx {
     double re, im;
 };
@@ -395,8 +438,9 @@ __device__ __forceinline__ EwRow ew_row(double vi, double dA, double dC, double 
 // column-major order (WITH_J only) with the same tiles and staging, each
 // record's slot filled by ew_record_csc and the diagonal entries
 // dQ_i/dtheta_i and dP_i/dv_i trading places.
-template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC>
-__device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
+// AHEAD (one state per workgroup, WITH_J): see read_ahead.
+template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC, bool AHEAD>
+__device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order, int ahead,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
     static_assert(WITH_J || !CSC, "the CSC order concerns J values");
@@ -639,6 +683,8 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
     // the record phase cover the gathers only.
     In first;
     load(sb, first);
+    Ahead later;
+    if constexpr (AHEAD) later = read_ahead<NT>(c, nb, ahead, sb, nstate, vm, va);
     const int irr = rowt ? ir : g.nb;  // lanes without a row read the inert entry
     const int2 rw = g.row_ew[irr];
     const double dA = g.dA[irr], dC = g.dC[irr];
@@ -701,25 +747,25 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
         }
     };
     pipelined_states<In, ONE>(sb, se, first, load, proc);
+    if constexpr (AHEAD) ahead_done(later);
 }
 
 // The injections of several states per workgroup are held to 80 registers
 // (their natural count is a few above), so that six waves fit per SIMD
-// instead of five.  The last parameter has one value; it keeps the kernel's
-// name as profiles record it.
-template <int NT, bool PAR, bool WITH_J, bool ONE, bool>
+// instead of five.
+template <int NT, bool PAR, bool WITH_J, bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((!ONE && !WITH_J) ? 6 : 1, 8)))
-    k_ew(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
+    k_ew(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm, const double *__restrict__ va,
          double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, WITH_J, ONE, false>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
+    ew_eval<NT, PAR, WITH_J, ONE, false, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, P, Q, J);
 }
 
 // Injections and J values in CSC order.
-template <int NT, bool PAR, bool ONE>
+template <int NT, bool PAR, bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(NT)
-    k_ew_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
+    k_ew_csc(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm,
              const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, true, ONE, true>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
+    ew_eval<NT, PAR, true, ONE, true, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, P, Q, J);
 }
 
 // ===================================================================
@@ -822,8 +868,8 @@ __device__ __forceinline__ void yb_phasor(const YbIn &x, Cx &V, Cx &U) {
 // evaluation of row j rounds them (CSC values = CSR values transposed, bit
 // for bit), and the diagonal entries dQ_i/dtheta_i and dP_i/dv_i trade
 // places.
-template <int NT, bool WITH_J, bool ONE, int PH, bool CSC>
-__device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
+template <int NT, bool WITH_J, bool ONE, int PH, bool CSC, bool AHEAD>
+__device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order, int ahead,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         const double *__restrict__ ph, double *__restrict__ P,
                                         double *__restrict__ Q, double *__restrict__ J) {
@@ -962,6 +1008,8 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
     auto load = [&](int s, In &x) { yb_load<PH, WITH_J>(vm, va, ph, n, (size_t)s * nb + j, x); };
     In first;  // first state's gathers before the row loads, as in k_ew
     load(sb, first);
+    Ahead later;
+    if constexpr (AHEAD) later = read_ahead<NT>(c, nb, ahead, sb, nstate, vm, va);
     const int irr = rowt ? ir : g.nb;
     const int2 rw = g.row_yb[irr];
     const int ra = lo16(rw.x), rz = hi16(rw.x), dd11 = ra + rw.y, dd12 = rz + rw.y;
@@ -1032,21 +1080,22 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
         }
     };
     pipelined_states<In, ONE>(sb, se, first, load, proc);
+    if constexpr (AHEAD) ahead_done(later);
 }
 
-template <int NT, bool WITH_J, bool ONE, int PH>
+template <int NT, bool WITH_J, bool ONE, int PH, bool AHEAD>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ONE ? 6 : 1, 8)))
-    k_ybus(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
+    k_ybus(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm, const double *__restrict__ va,
            const double *__restrict__ ph, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    yb_eval<NT, WITH_J, ONE, PH, false>(g, nstate, spb, nchunk, order, vm, va, ph, P, Q, J);
+    yb_eval<NT, WITH_J, ONE, PH, false, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, ph, P, Q, J);
 }
 
 // Injections and J values in CSC order by the Ybus method.
-template <int NT, bool ONE>
+template <int NT, bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ONE ? 6 : 1, 8)))
-    k_ybus_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
+    k_ybus_csc(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm,
                const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    yb_eval<NT, true, ONE, PH_FLY, true>(g, nstate, spb, nchunk, order, vm, va, nullptr, P, Q, J);
+    yb_eval<NT, true, ONE, PH_FLY, true, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, nullptr, P, Q, J);
 }
 
 // ===================================================================
@@ -1651,21 +1700,27 @@ __global__ void k_lane_fill(DevLaneFill f, bool ew) {
     }
 }
 
+// Launches with read-ahead (L.ahead, one state per workgroup) run the AHEAD
+// instantiations: the others stay free of its registers.
 template <int NT, bool ONE, bool WITH_J>
 void launch_ybus_ph(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
     double *J = WITH_J ? L.jval : nullptr;
     switch (L.phasor) {
         case PH_SPLIT:
-            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_SPLIT>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
-                               L.vm, L.va, L.ph, L.p, L.q, J);
+            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_SPLIT, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
+                               L.order, 0, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
         case PH_INTERLEAVED:
-            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_INTERLEAVED>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                               L.order, L.vm, L.va, L.ph, L.p, L.q, J);
+            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_INTERLEAVED, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
+                               L.order, 0, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
         default:
-            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
-                               L.vm, L.va, L.ph, L.p, L.q, J);
+            if (ONE && WITH_J && L.ahead)
+                hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, ONE && WITH_J>), grid, block, 0, st, g, L.nstate, spb,
+                                   nchunk, L.order, L.ahead, L.vm, L.va, L.ph, L.p, L.q, J);
+            else
+                hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
+                                   L.order, 0, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
     }
 }
@@ -1675,13 +1730,37 @@ hipError_t launch_ybus(const DevGrid &g, const Launch &L, dim3 grid, dim3 block,
     if (L.phasor != PH_FLY && L.phasor != PH_SPLIT && L.phasor != PH_INTERLEAVED) return hipErrorInvalidValue;
     if (L.kind == K_YB_SJ_CSC) {
         if (L.phasor != PH_FLY) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_ybus_csc<NT, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
-                           L.p, L.q, L.jval);
+        if (ONE && L.ahead)
+            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.ahead,
+                               L.vm, L.va, L.p, L.q, L.jval);
+        else
+            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+                               L.va, L.p, L.q, L.jval);
     } else if (L.kind == K_YB_SJ)
         launch_ybus_ph<NT, ONE, true>(g, L, grid, block, spb, nchunk, st);
     else
         launch_ybus_ph<NT, ONE, false>(g, L, grid, block, spb, nchunk, st);
     return hipGetLastError();
+}
+
+template <int NT, bool ONE, bool PAR>
+void launch_ew(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
+    const bool ahead = ONE && L.ahead != 0;
+    if (L.kind == K_EW_S)
+        hipLaunchKernelGGL((k_ew<NT, PAR, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+                           L.va, L.p, L.q, nullptr);
+    else if (L.kind == K_EW_SJ && ahead)
+        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.ahead,
+                           L.vm, L.va, L.p, L.q, L.jval);
+    else if (L.kind == K_EW_SJ)
+        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+                           L.va, L.p, L.q, L.jval);
+    else if (ahead)
+        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.ahead,
+                           L.vm, L.va, L.p, L.q, L.jval);
+    else
+        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+                           L.va, L.p, L.q, L.jval);
 }
 
 template <int NT, bool ONE>
@@ -1696,28 +1775,12 @@ hipError_t launch_nt(const DevGrid &g, const Launch &L, hipStream_t st) {
     const dim3 grid((unsigned)blocks), block(NT);
     switch (L.kind) {
         case K_EW_S:
-            if (L.has_parallel)
-                hipLaunchKernelGGL((k_ew<NT, true, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
-                                   L.vm, L.va, L.p, L.q, nullptr);
-            else
-                hipLaunchKernelGGL((k_ew<NT, false, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order,
-                                   L.vm, L.va, L.p, L.q, nullptr);
-            break;
         case K_EW_SJ:
-            if (L.has_parallel)
-                hipLaunchKernelGGL((k_ew<NT, true, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
-                                   L.p, L.q, L.jval);
-            else
-                hipLaunchKernelGGL((k_ew<NT, false, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va,
-                                   L.p, L.q, L.jval);
-            break;
         case K_EW_SJ_CSC:
             if (L.has_parallel)
-                hipLaunchKernelGGL((k_ew_csc<NT, true, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
-                                   L.va, L.p, L.q, L.jval);
+                launch_ew<NT, ONE, true>(g, L, grid, block, spb, nchunk, st);
             else
-                hipLaunchKernelGGL((k_ew_csc<NT, false, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
-                                   L.va, L.p, L.q, L.jval);
+                launch_ew<NT, ONE, false>(g, L, grid, block, spb, nchunk, st);
             break;
         case K_YB_S:
         case K_YB_SJ:
@@ -1748,17 +1811,17 @@ int occupancy_nt(int kind, bool par) {
                   : reinterpret_cast<const void *>(&k_ew<NT, false, true, ONE, false>));
             break;
         case K_EW_SJ_CSC:
-            q(par ? reinterpret_cast<const void *>(&k_ew_csc<NT, true, ONE>)
-                  : reinterpret_cast<const void *>(&k_ew_csc<NT, false, ONE>));
+            q(par ? reinterpret_cast<const void *>(&k_ew_csc<NT, true, ONE, false>)
+                  : reinterpret_cast<const void *>(&k_ew_csc<NT, false, ONE, false>));
             break;
         case K_YB_S:
-            q(reinterpret_cast<const void *>(&k_ybus<NT, false, ONE, PH_FLY>));
+            q(reinterpret_cast<const void *>(&k_ybus<NT, false, ONE, PH_FLY, false>));
             break;
         case K_YB_SJ:
-            q(reinterpret_cast<const void *>(&k_ybus<NT, true, ONE, PH_FLY>));
+            q(reinterpret_cast<const void *>(&k_ybus<NT, true, ONE, PH_FLY, false>));
             break;
         case K_YB_SJ_CSC:
-            q(reinterpret_cast<const void *>(&k_ybus_csc<NT, ONE>));
+            q(reinterpret_cast<const void *>(&k_ybus_csc<NT, ONE, false>));
             break;
         case K_EW_VJP:
             q(reinterpret_cast<const void *>(&k_ew_vjp<NT, ONE>));
