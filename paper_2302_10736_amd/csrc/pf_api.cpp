@@ -987,6 +987,7 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
 // an XCD's 32 compute units) has in flight.  The states read ahead have to
 // stay in the XCD's L2 until they are used: 3 of its 4 MB.
 int ahead_of(const pf_grid *g, const pf::Launch &L) {
+    if (L.nstate < 10) return 0;
     if (!is_jacobian(L.kind) || L.phasor != pf::PH_FLY || L.states_per_block != 1 || L.order != pf::WO_GROUPED) return 0;
     const bool yb = L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
     const int64_t walk = ((int64_t)(yb ? g->ytiles : g->tiles).size() + 7) / 8;  // tiles per XCD and state

@@ -177,7 +177,8 @@ constexpr int kRsrcFlags = 0x00027000;  // raw buffer descriptor, 32-bit data
 // their own work is done, read one word of each 128-byte line of their rows'
 // states s + dist .. s + dist + burst - 1 into the XCD's L2 (state 0's also
 // the states before those), and the workgroups in between find their states
-// there.  `ahead` holds burst (a power of two) and dist << 8, or 0 for none.
+// there.  `ahead` holds burst (a power of two) and dist << 8; it travels above
+// the low four bits of the kernels' `order`.
 // Same tile, later states: the neighbours' rows come from the neighbouring
 // tiles' workgroups, which the grouped order keeps on the same XCD.
 struct Ahead {
@@ -188,7 +189,7 @@ template <int NT>
 __device__ __forceinline__ Ahead read_ahead(const Tile &c, size_t nb, int ahead, int s, int nstate, const double *vm,
                                             const double *va) {
     const int burst = ahead & 0xff, dist = ahead >> 8;
-    const bool on = burst != 0 && (s & (burst - 1)) == 0;
+    const bool on = (s & (burst - 1)) == 0;
     const int first = s == 0 ? 1 : s + dist;
     const int lines = (c.nrows + 15) / 16 + 1;  // a row range of any alignment
     const int lg = 32 - __builtin_clz(lines - 1);
@@ -440,7 +441,7 @@ __device__ __forceinline__ EwRow ew_row(double vi, double dA, double dC, double 
 // dQ_i/dtheta_i and dP_i/dv_i trading places.
 // AHEAD (one state per workgroup, WITH_J): see read_ahead.
 template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC, bool AHEAD>
-__device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order, int ahead,
+__device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
     static_assert(WITH_J || !CSC, "the CSC order concerns J values");
@@ -455,7 +456,7 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
     __shared__ double s_rem[NBUF][4][NR];
 
     int t, c0;
-    if (!work_item(g.ntiles, nchunk, order, t, c0)) return;
+    if (!work_item(g.ntiles, nchunk, AHEAD ? (int)WO_GROUPED : order, t, c0)) return;
     const int sb = c0 * spb;
     const int se = min(nstate, sb + spb);
     const int k = threadIdx.x;
@@ -684,7 +685,7 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
     In first;
     load(sb, first);
     Ahead later;
-    if constexpr (AHEAD) later = read_ahead<NT>(c, nb, ahead, sb, nstate, vm, va);
+    if constexpr (AHEAD) later = read_ahead<NT>(c, nb, order >> 4, sb, nstate, vm, va);
     const int irr = rowt ? ir : g.nb;  // lanes without a row read the inert entry
     const int2 rw = g.row_ew[irr];
     const double dA = g.dA[irr], dC = g.dC[irr];
@@ -755,17 +756,17 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
 // instead of five.
 template <int NT, bool PAR, bool WITH_J, bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((!ONE && !WITH_J) ? 6 : 1, 8)))
-    k_ew(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm, const double *__restrict__ va,
+    k_ew(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
          double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, WITH_J, ONE, false, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, P, Q, J);
+    ew_eval<NT, PAR, WITH_J, ONE, false, AHEAD>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
 }
 
 // Injections and J values in CSC order.
 template <int NT, bool PAR, bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(NT)
-    k_ew_csc(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm,
+    k_ew_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
              const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, true, ONE, true, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, P, Q, J);
+    ew_eval<NT, PAR, true, ONE, true, AHEAD>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
 }
 
 // ===================================================================
@@ -869,7 +870,7 @@ __device__ __forceinline__ void yb_phasor(const YbIn &x, Cx &V, Cx &U) {
 // for bit), and the diagonal entries dQ_i/dtheta_i and dP_i/dv_i trade
 // places.
 template <int NT, bool WITH_J, bool ONE, int PH, bool CSC, bool AHEAD>
-__device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order, int ahead,
+__device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         const double *__restrict__ ph, double *__restrict__ P,
                                         double *__restrict__ Q, double *__restrict__ J) {
@@ -881,7 +882,7 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
     __shared__ __align__(16) double s_J[NBUF][WITH_J ? kJStage<NT> : 2];
 
     int t, c0;
-    if (!work_item(g.nytiles, nchunk, order, t, c0)) return;
+    if (!work_item(g.nytiles, nchunk, AHEAD ? (int)WO_GROUPED : order, t, c0)) return;
     const int sb = c0 * spb;
     const int se = min(nstate, sb + spb);
     const int k = threadIdx.x;
@@ -1009,7 +1010,7 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
     In first;  // first state's gathers before the row loads, as in k_ew
     load(sb, first);
     Ahead later;
-    if constexpr (AHEAD) later = read_ahead<NT>(c, nb, ahead, sb, nstate, vm, va);
+    if constexpr (AHEAD) later = read_ahead<NT>(c, nb, order >> 4, sb, nstate, vm, va);
     const int irr = rowt ? ir : g.nb;
     const int2 rw = g.row_yb[irr];
     const int ra = lo16(rw.x), rz = hi16(rw.x), dd11 = ra + rw.y, dd12 = rz + rw.y;
@@ -1085,17 +1086,17 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
 
 template <int NT, bool WITH_J, bool ONE, int PH, bool AHEAD>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ONE ? 6 : 1, 8)))
-    k_ybus(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm, const double *__restrict__ va,
+    k_ybus(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
            const double *__restrict__ ph, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    yb_eval<NT, WITH_J, ONE, PH, false, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, ph, P, Q, J);
+    yb_eval<NT, WITH_J, ONE, PH, false, AHEAD>(g, nstate, spb, nchunk, order, vm, va, ph, P, Q, J);
 }
 
 // Injections and J values in CSC order by the Ybus method.
 template <int NT, bool ONE, bool AHEAD>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ONE ? 6 : 1, 8)))
-    k_ybus_csc(DevGrid g, int nstate, int spb, int nchunk, int order, int ahead, const double *__restrict__ vm,
+    k_ybus_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
                const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    yb_eval<NT, true, ONE, PH_FLY, true, AHEAD>(g, nstate, spb, nchunk, order, ahead, vm, va, nullptr, P, Q, J);
+    yb_eval<NT, true, ONE, PH_FLY, true, AHEAD>(g, nstate, spb, nchunk, order, vm, va, nullptr, P, Q, J);
 }
 
 // ===================================================================
@@ -1704,23 +1705,24 @@ __global__ void k_lane_fill(DevLaneFill f, bool ew) {
 // instantiations: the others stay free of its registers.
 template <int NT, bool ONE, bool WITH_J>
 void launch_ybus_ph(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
+    const int order = L.order | L.ahead << 4;
     double *J = WITH_J ? L.jval : nullptr;
     switch (L.phasor) {
         case PH_SPLIT:
             hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_SPLIT, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                               L.order, 0, L.vm, L.va, L.ph, L.p, L.q, J);
+                               L.order, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
         case PH_INTERLEAVED:
             hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_INTERLEAVED, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                               L.order, 0, L.vm, L.va, L.ph, L.p, L.q, J);
+                               L.order, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
         default:
             if (ONE && WITH_J && L.ahead)
                 hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, ONE && WITH_J>), grid, block, 0, st, g, L.nstate, spb,
-                                   nchunk, L.order, L.ahead, L.vm, L.va, L.ph, L.p, L.q, J);
+                                   nchunk, order, L.vm, L.va, L.ph, L.p, L.q, J);
             else
                 hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                                   L.order, 0, L.vm, L.va, L.ph, L.p, L.q, J);
+                                   L.order, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
     }
 }
@@ -1730,11 +1732,12 @@ hipError_t launch_ybus(const DevGrid &g, const Launch &L, dim3 grid, dim3 block,
     if (L.phasor != PH_FLY && L.phasor != PH_SPLIT && L.phasor != PH_INTERLEAVED) return hipErrorInvalidValue;
     if (L.kind == K_YB_SJ_CSC) {
         if (L.phasor != PH_FLY) return hipErrorInvalidValue;
+        const int order = L.order | L.ahead << 4;
         if (ONE && L.ahead)
-            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.ahead,
+            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
                                L.vm, L.va, L.p, L.q, L.jval);
         else
-            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
                                L.va, L.p, L.q, L.jval);
     } else if (L.kind == K_YB_SJ)
         launch_ybus_ph<NT, ONE, true>(g, L, grid, block, spb, nchunk, st);
@@ -1746,20 +1749,21 @@ hipError_t launch_ybus(const DevGrid &g, const Launch &L, dim3 grid, dim3 block,
 template <int NT, bool ONE, bool PAR>
 void launch_ew(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
     const bool ahead = ONE && L.ahead != 0;
+    const int order = L.order | L.ahead << 4;
     if (L.kind == K_EW_S)
-        hipLaunchKernelGGL((k_ew<NT, PAR, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+        hipLaunchKernelGGL((k_ew<NT, PAR, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
                            L.va, L.p, L.q, nullptr);
     else if (L.kind == K_EW_SJ && ahead)
-        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.ahead,
+        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
                            L.vm, L.va, L.p, L.q, L.jval);
     else if (L.kind == K_EW_SJ)
-        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
                            L.va, L.p, L.q, L.jval);
     else if (ahead)
-        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.ahead,
+        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
                            L.vm, L.va, L.p, L.q, L.jval);
     else
-        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, 0, L.vm,
+        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
                            L.va, L.p, L.q, L.jval);
 }
 

@@ -52,3 +52,33 @@ def test_read_ahead_same_bits(grid_6k, tile, nstate):
         torch.cuda.synchronize()
         for a, b in zip(got[pf.PF_ORDER_GROUPED], got[pf.PF_ORDER_TILE_MAJOR]):
             assert torch.equal(a, b)
+
+
+# Branches below, at and past a wave's 48 outputs and a workgroup's 192, with
+# rows that start at every place of a 128-byte line (nl odd).
+@pytest.mark.parametrize("nl,nstate,off", [(1, 2, 0), (47, 3, 1), (48, 17, 0), (49, 16, 5), (176, 2, 15), (177, 3, 0),
+                                           (191, 9, 3), (193, 16, 2), (385, 5, 7)])
+def test_flow_rows_any_alignment(nl, nstate, off):
+    import oracle
+    import torch
+    _gpu.require_gpu()
+    nb = max(2, int(nl / 1.3))
+    g = gridgen.make_grid(nb, max(nl, nb - 1), 0.3, case=9, grid=nl)
+    G = pf.Grid.from_grid(g)
+    vm, va = gridgen.states(nb, nstate, case=9, grid=nl)
+    pad = 64  # values around every output, which stay as they are
+    def out(*shape):
+        n = int(np.prod(shape))
+        whole = torch.full((n + 2 * pad + off,), -7.0, dtype=torch.float64, device="cuda:0")
+        return whole, whole[pad + off:pad + off + n].view(shape)
+    outs = [out(nstate, g.nl) for _ in range(4)] + [out(nstate, 16, g.nl)]
+    pf.pf_branch_flows(G, _gpu.to_dev(vm), _gpu.to_dev(va), *[o for _, o in outs])
+    torch.cuda.synchronize()
+    for whole, o in outs:
+        assert (whole[:pad + off] == -7.0).all() and (whole[pad + off + o.numel():] == -7.0).all()
+    got = [o.cpu().numpy() for _, o in outs]
+    for s in range(nstate):
+        want = oracle.branch_flows(g, vm[s], va[s])
+        for a, b in zip(got[:4], want):
+            assert _gpu.rel_err(a[s], b) <= _gpu.TOL
+        assert _gpu.rel_err(got[4][s], np.asarray(oracle.branch_flow_jac(g, vm[s], va[s])).reshape(got[4][s].shape)) <= _gpu.TOL
