@@ -1421,9 +1421,8 @@ struct EndVals {
     double p, q, dpti, dpvi, dqti, dqvi, dptj, dpvj, dqtj, dqvj;
 };
 
-__device__ __forceinline__ EndVals branch_end(double vi, double vj, double d, double A, double C, double G, double B) {
-    double sn, cs;
-    sincos_dev(d, &sn, &cs);
+__device__ __forceinline__ EndVals branch_end(double vi, double vj, double sn, double cs, double A, double C, double G,
+                                              double B) {
     const double al = fma(G, cs, B * sn), be = fma(G, sn, -(B * cs));
     const double w = vi * vj;
     EndVals o;
@@ -1471,9 +1470,20 @@ __global__ void k_branch_consts(DevTwoPhase d, double *__restrict__ bc) {
     bc[5 * n + l] = c.Ct;
 }
 
-// Both ends of branch l (from end first) at one state.  PRE reads the
-// precomputed constants (56 bytes per branch with the shift) instead of
-// deriving them from the parameters (40 bytes); the values are the same.
+// Both ends of a branch (from end first) at one state.  The to end's angle
+// tk - th + phi is the exact negative of the from end's, the sine odd and the
+// cosine even bit for bit, so one evaluation serves both.
+__device__ __forceinline__ void branch_ends(const BranchConsts &c, double phi, double vh, double th, double vk, double tk,
+                                            EndVals &f, EndVals &t) {
+    double sn, cs;
+    sincos_dev(th - tk - phi, &sn, &cs);
+    f = branch_end(vh, vk, sn, cs, c.Af, c.Cf, c.G, c.B);
+    t = branch_end(vk, vh, -sn, cs, c.At, c.Ct, c.G, c.B);
+}
+
+// Branch l of the baselines.  PRE reads the precomputed constants (56 bytes
+// per branch with the shift) instead of deriving them from the parameters (40
+// bytes); the values are the same.
 template <bool PRE = false>
 __device__ __forceinline__ void branch_ends(const DevTwoPhase &d, int l, const double *vm, const double *va,
                                             EndVals &f, EndVals &t) {
@@ -1485,10 +1495,7 @@ __device__ __forceinline__ void branch_ends(const DevTwoPhase &d, int l, const d
     } else {
         c = branch_consts(d.r[l], d.x[l], d.b[l], d.tap[l]);
     }
-    const double phi = d.shift[l];
-    const double vh = vm[h], th = va[h], vk = vm[k], tk = va[k];
-    f = branch_end(vh, vk, th - tk - phi, c.Af, c.Cf, c.G, c.B);
-    t = branch_end(vk, vh, tk - th + phi, c.At, c.Ct, c.G, c.B);
+    branch_ends(c, d.shift[l], vm[h], va[h], vm[k], va[k], f, t);
 }
 
 // Plain stores: the reduction kernel reads the scratch right after, from cache.
@@ -1515,30 +1522,54 @@ __global__ void k_tp_branch(DevTwoPhase d, const double *__restrict__ vm, const 
     tp_store(d.scr, d.nrec, d.br_rec[2 * l + 1], t);
 }
 
-// Branch flows and (WITH_J) their 16 partials: one thread per (branch,
-// state); every output array is written with consecutive branches in
-// consecutive lanes.
+// Branch flows and (WITH_J) their 16 partials: one lane per (branch, state),
+// 20 output rows of nl values each.  Bound by the stores: a row starts at any
+// multiple of 8 bytes, and a wave's 64 values then cover two partial 128-byte
+// lines for every three or four whole ones, each partial line a memory write
+// of its own.  So a wave evaluates 64 branches, the first 16 of them also the
+// last 16 of the wave before, and stores the 48 whose place in the row makes
+// up three whole lines; the workgroups of neighbouring branches run on one
+// XCD.  41,115 branches x 24 states: 51.8 -> 32.1 us (5.3 TB/s; whole lines
+// without the XCD order 46.4, the order alone 52.2, 256-branch workgroups
+// aligned as a whole 44.5, two or three states per lane 34.6 and 35.3).
+constexpr int kFlowWave = 48, kFlowBack = 16, kFlowBlock = 4 * kFlowWave;
+
 template <bool WITH_J>
-__global__ void k_flows(DevTwoPhase d, int nstate, const double *__restrict__ vm, const double *__restrict__ va,
-                        double *__restrict__ pf, double *__restrict__ qf, double *__restrict__ pt,
-                        double *__restrict__ qt, double *__restrict__ jac) {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= d.nl) return;
-    for (int s = blockIdx.y; s < nstate; s += gridDim.y) {
-        const size_t sb = (size_t)s * d.nb, sl = (size_t)s * d.nl;
+__global__ void __launch_bounds__(256)
+    k_flows(DevTwoPhase d, int nstate, int nsb, const double *__restrict__ vm, const double *__restrict__ va,
+            double *__restrict__ pf, double *__restrict__ qf, double *__restrict__ pt, double *__restrict__ qt,
+            double *__restrict__ jac) {
+    const int nlb = (d.nl + kFlowBlock + kFlowBack - 1) / kFlowBlock;
+    const int w = work_index(gridDim.x);
+    const int s0 = w / nlb, lb = w - s0 * nlb;
+    if (s0 >= nsb) return;
+    const int out0 = lb * kFlowBlock + (int)(threadIdx.x / 64) * kFlowWave;  // the wave's outputs, before the row's shift
+    const int lr = out0 - kFlowBack + (int)(threadIdx.x & 63);
+    const bool in = lr >= 0 && lr < d.nl;
+    const int l = min(max(lr, 0), d.nl - 1);
+    const int h = d.br_from[l], k = d.br_to[l];
+    const size_t n = (size_t)d.nl;
+    const BranchConsts c = {d.bc[l], d.bc[n + l], d.bc[2 * n + l], d.bc[3 * n + l], d.bc[4 * n + l], d.bc[5 * n + l]};
+    const double phi = d.shift[l];
+    for (int s = s0; s < nstate; s += nsb) {
+        const double *vms = vm + (size_t)s * d.nb, *vas = va + (size_t)s * d.nb;
         EndVals f, t;
-        branch_ends(d, l, vm + sb, va + sb, f, t);
-        st_out(pf + sl + l, f.p);
-        st_out(qf + sl + l, f.q);
-        st_out(pt + sl + l, t.p);
-        st_out(qt + sl + l, t.q);
+        branch_ends(c, phi, vms[h], vas[h], vms[k], vas[k], f, t);
+        auto put = [&](double *row, double v) {
+            const int first = out0 - ((int)((uintptr_t)(row + out0) >> 3) & 15);  // where a line starts
+            if (in && lr >= first && lr < first + kFlowWave) st_out(row + lr, v);
+        };
+        put(pf + s * n, f.p);
+        put(qf + s * n, f.q);
+        put(pt + s * n, t.p);
+        put(qt + s * n, t.q);
         if constexpr (WITH_J) {
             // rows d(Pf, Qf, Pt, Qt) / d(theta_from, theta_to, v_from, v_to)
             const double v[16] = {f.dpti, f.dptj, f.dpvi, f.dpvj, f.dqti, f.dqtj, f.dqvi, f.dqvj,
                                   t.dptj, t.dpti, t.dpvj, t.dpvi, t.dqtj, t.dqti, t.dqvj, t.dqvi};
-            double *js = jac + (size_t)s * 16 * d.nl;
+            double *js = jac + (size_t)s * 16 * n;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) st_out(js + (size_t)q * d.nl + l, v[q]);
+            for (int q = 0; q < 16; ++q) put(js + (size_t)q * n, v[q]);
         }
     }
 }
@@ -1976,11 +2007,14 @@ hipError_t launch_copy_add(const DevTwoPhase &d, int32_t nstate, int64_t nnz_j, 
 hipError_t launch_flows(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
                         double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
     if (d.nl == 0 || nstate == 0) return hipSuccess;
-    const dim3 grid((unsigned)((d.nl + 255) / 256), (unsigned)std::min<int32_t>(nstate, 65535));
+    // One state per workgroup while the grid allows it.
+    const int64_t nlb = ((int64_t)d.nl + kFlowBlock + kFlowBack - 1) / kFlowBlock;
+    const int nsb = (int)std::min<int64_t>(nstate, std::max<int64_t>(1, ((int64_t)1 << 30) / nlb));
+    const dim3 grid((unsigned)((nlb * nsb + kXcds - 1) / kXcds * kXcds));
     if (jac)
-        hipLaunchKernelGGL(k_flows<true>, grid, dim3(256), 0, stream, d, nstate, vm, va, pf, qf, pt, qt, jac);
+        hipLaunchKernelGGL(k_flows<true>, grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
     else
-        hipLaunchKernelGGL(k_flows<false>, grid, dim3(256), 0, stream, d, nstate, vm, va, pf, qf, pt, qt, jac);
+        hipLaunchKernelGGL(k_flows<false>, grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
     return hipGetLastError();
 }
 
