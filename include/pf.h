@@ -298,7 +298,7 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     element-wise work tile, Ybus nonzeros per Ybus tile
  *   states_per_block  voltage states one workgroup evaluates in turn, with
  *                     the tile's constants held in registers (>= 1; 0 =
- *                     automatic: at most 2 for Jacobian launches, at most 8
+ *                     automatic: at most 4 for Jacobian launches, at most 8
  *                     for injections, fewer when the tiles alone do not
  *                     fill the GPU; the adjoint splits each tile's states
  *                     into as many chunks as fill one round of resident

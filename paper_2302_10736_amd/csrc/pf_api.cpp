@@ -945,7 +945,7 @@ int work_order(const pf_grid *g, int kind) {
 // registers and walks its states one after another, so fewer, longer
 // workgroups read the constants fewer times, while more, shorter workgroups
 // keep more of every state's output stream in flight.  The automatic choice
-// takes at most 2 states per workgroup for Jacobian launches (their time is
+// takes at most 4 states per workgroup for Jacobian launches (their time is
 // the J stream: 8 nnzJ bytes per state against a few bytes of constants),
 // 1 when the tables a workgroup's XCD walks stay in its 4 MB L2 between
 // states (an eighth of them in the grouped order, all otherwise), and at
@@ -968,12 +968,14 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     chunks = std::min<int64_t>(chunks, nstate);
     const int fill = (int)((nstate + chunks - 1) / chunks);
     if (is_jacobian(kind)) {
-        // One state per workgroup (the lean single-state kernel) when the
-        // tile tables an XCD walks stay in its L2 across states (an eighth
-        // of them in the grouped order); else two.
+        // One state per workgroup (the single-state kernel) when the tile
+        // tables an XCD walks stay in its L2 across states (an eighth of
+        // them in the grouped order); else up to four per read of the tables
+        // (64 grids of 1k to 80k buses x 4 states: 170 us at two, 158 at
+        // four; 300k buses x 16: 153 and 146).
         int64_t tb = table_bytes(g, kind);
         if (work_order(g, kind) == pf::WO_GROUPED) tb /= 8;
-        return std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 2);
+        return std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4);
     }
     if (kind == pf::K_EW_VJP) return fill;
     return std::min(fill, 8);

@@ -284,6 +284,27 @@ __device__ __forceinline__ void pipelined_states(int sb, int se, In &ra, Load &&
     }
 }
 
+// Several states with J: one register set and one LDS buffer, each state
+// loaded when the one before is done (a third barrier keeps its J rows until
+// they are written).  Half the LDS and 10 to 18 registers less than the
+// pipelined loop let five workgroups per compute unit hide each other's loads
+// where four (three with parallel branches) prefetched their own: 300k buses x
+// 16 states 161 -> 153 us, 300k x 3 with parallel circuits 43.1 -> 33.1 us, 64
+// grids of 1k to 80k buses x 4 states 181 -> 170 us.
+template <class In, bool ONE, bool WITH_J, class Load, class Proc>
+__device__ __forceinline__ void states_loop(int sb, int se, In &ra, Load &&load, Proc &&proc) {
+    if constexpr (ONE || !WITH_J) {
+        pipelined_states<In, ONE>(sb, se, ra, load, proc);
+    } else {
+        for (int s = sb;;) {
+            proc(s, 0, ra);
+            if (++s >= se) break;
+            load(s, ra);
+            lds_barrier();
+        }
+    }
+}
+
 // Row sums of two LDS arrays over records [a, z), strictly left to right,
 // continuing the running sums u and v.  Records are read four at a time so
 // one LDS round trip serves four terms; the last zero to three records of
@@ -446,7 +467,7 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
                                         double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
     static_assert(WITH_J || !CSC, "the CSC order concerns J values");
     constexpr int NR = (WITH_J && PAR) ? NT : 1;  // remote partials kept for slot sums
-    constexpr int NBUF = ONE ? 1 : 2;             // LDS buffers alternate between states
+    constexpr int NBUF = ONE || WITH_J ? 1 : 2;   // injections alternate between two LDS buffers
     constexpr int NS = kEwSlots(NT);              // Ybus slots per tile
     __shared__ int s_ls[NT];   // long rows: local slot of each branch end of a piece
     __shared__ int s_cls[2];    // long rows: slot carried into the next piece (-1: none), by piece parity
@@ -747,7 +768,7 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
             write_jrows<NT, NS>(c, s_J[p], J + (size_t)s * (size_t)g.nnz_j);
         }
     };
-    pipelined_states<In, ONE>(sb, se, first, load, proc);
+    states_loop<In, ONE, WITH_J>(sb, se, first, load, proc);
     if constexpr (AHEAD) ahead_done(later);
 }
 
@@ -875,7 +896,7 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
                                         const double *__restrict__ ph, double *__restrict__ P,
                                         double *__restrict__ Q, double *__restrict__ J) {
     static_assert(!CSC || (WITH_J && PH == PH_FLY), "the CSC order concerns J values");
-    constexpr int NBUF = ONE ? 1 : 2;
+    constexpr int NBUF = ONE || WITH_J ? 1 : 2;
     __shared__ double s_yv[NBUF][2][NT];  // Y_ij V_j
     __shared__ double s_vu[NBUF][4][NT];  // per row: V_i, U_i (re, im)
     __shared__ double s_yd[WITH_J ? 2 : 1][WITH_J ? NT : 1];  // per row: Y_ii (state-free, written once)
@@ -1080,7 +1101,7 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
             write_jrows<NT, NT>(c, s_J[p], J + (size_t)s * (size_t)g.nnz_j);
         }
     };
-    pipelined_states<In, ONE>(sb, se, first, load, proc);
+    states_loop<In, ONE, WITH_J>(sb, se, first, load, proc);
     if constexpr (AHEAD) ahead_done(later);
 }
 

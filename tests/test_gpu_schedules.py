@@ -82,3 +82,30 @@ def test_flow_rows_any_alignment(nl, nstate, off):
         for a, b in zip(got[:4], want):
             assert _gpu.rel_err(a[s], b) <= _gpu.TOL
         assert _gpu.rel_err(got[4][s], np.asarray(oracle.branch_flow_jac(g, vm[s], va[s])).reshape(got[4][s].shape)) <= _gpu.TOL
+
+
+# States per workgroup of the Jacobian loop: one, a few, more than there are.
+@pytest.mark.parametrize("tile", [64, 256, 512])
+@pytest.mark.parametrize("parallel", [False, True])
+def test_jacobian_states_per_workgroup_same_bits(tile, parallel):
+    import torch
+    _gpu.require_gpu()
+    g = gridgen.make_grid(1_501, 2_100, 0.15, case=9, grid=1)
+    if parallel:
+        cat = lambda x: np.concatenate([x, x[::7]])  # noqa: E731
+        g = gridgen.Grid(g.nb, len(cat(g.fbus)), *[cat(x) for x in (g.fbus, g.tbus, g.r, g.x, g.b, g.tap, g.shift)], g.gs, g.bs)
+    G = pf.Grid.from_grid(g)
+    pf.pf_ybus(G)
+    nstate = 7
+    vm, va = (_gpu.to_dev(x) for x in gridgen.states(g.nb, nstate, case=9, grid=1))
+    for method in METHODS:
+        want = None
+        for spb in (1, 2, 3, 4, 7, 9):
+            G.set_schedule(tile, spb, pf.PF_ORDER_AUTO)
+            p, q = torch.empty_like(vm), torch.empty_like(vm)
+            j = torch.empty((nstate, G.nnz_j), dtype=torch.float64, device="cuda:0")
+            pf.pf_jacobian_values(G, method, vm, va, p, q, j)
+            torch.cuda.synchronize()
+            if want is None:
+                want = (p, q, j)
+            assert all(torch.equal(a, b) for a, b in zip((p, q, j), want))
