@@ -298,11 +298,10 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     element-wise work tile, Ybus nonzeros per Ybus tile
  *   states_per_block  voltage states one workgroup evaluates in turn, with
  *                     the tile's constants held in registers (>= 1; 0 =
- *                     automatic: at most 4 for Jacobian launches, at most 8
- *                     for injections, fewer when the tiles alone do not
- *                     fill the GPU; the adjoint splits each tile's states
- *                     into as many chunks as fill one round of resident
- *                     workgroups)
+ *                     automatic: at most 4 for Jacobian launches, 8 for
+ *                     injections and 16 for the adjoint, fewer when the tiles
+ *                     alone do not fill the GPU; with PF_ORDER_AUTO on grids
+ *                     numbered without regard to the network 1 or 2)
  *   order             order of the (tile, state chunk) work items over the
  *                     workgroups: PF_ORDER_TILE_MAJOR (the state chunks of
  *                     one tile are adjacent), PF_ORDER_STATE_MAJOR (the tiles
@@ -312,10 +311,11 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     of the tiles and walks them chunk by chunk: the tiles'
  *                     tables stay in its L2 while neighbouring workgroups
  *                     write neighbouring parts of J) or PF_ORDER_AUTO
- *                     (Jacobian launches: grouped, state-major when the
- *                     tile tables are below 512 KB; injections and the
- *                     adjoint: tile-major, so the state chunks of one tile
- *                     share an L2)
+ *                     (Jacobian launches and the adjoint: grouped, below
+ *                     512 KB of tile tables state-major and tile-major;
+ *                     injections: tile-major, so the state chunks of one
+ *                     tile share an L2; all of them state-major on grids
+ *                     numbered without regard to the network)
  * The initial schedule is tile_items 256 (with several grids per handle:
  * the smallest of 64, 128, 256 that holds the mean branch ends per grid,
  * since tiles never span grids), states_per_block 0, PF_ORDER_AUTO.

@@ -13,6 +13,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <new>
 #include <string>
@@ -80,6 +81,7 @@ struct pf_grid {
 
     int32_t tile_items = 256, states_per_block = 0, order = PF_ORDER_AUTO;
     std::vector<pf::TileDesc> tiles, ytiles;  // element-wise and Ybus work tiles
+    bool scattered = false;                   // most branches join buses of distant numbers (see work_order)
     int32_t num_cus = 0;
     pf::DevLaneFill lanes{};  // gather sources and targets of the lane values
     pf::DevTwoPhase tp{};     // two-phase element-wise tables and scratch (inside dmem)
@@ -521,6 +523,12 @@ int pf_build_pattern(int32_t nb, int32_t nl, const int32_t *fbus, const int32_t 
             g->yrow[i + 1] = (int32_t)g->ycol.size();
         }
         g->nnz_y = (int64_t)g->ycol.size();
+        // Numbering: along the network nearly every branch joins buses at
+        // most a few hundred apart.
+        constexpr int32_t kFar = 512;
+        int64_t far = 0;
+        for (int64_t p = 0; p < g->nnz_y; ++p) far += std::abs(g->ycol[p] - g->slot_row[p]) > kFar;
+        g->scattered = 2 * far > g->nnz_y - nb;
         g->slot_item.push_back((int32_t)ni);
         g->has_parallel = g->nnz_y != ni;
         g->y_off.assign(ngrids + 1, 0);
@@ -923,9 +931,17 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 // rows, and later states can be read ahead, see ahead_of); state-major for
 // grids of tables below 512 KB, whose eighth would be fewer than eight tiles
 // (2,383 buses x 250 states, Ybus: 20.4 us state-major, 21.0 grouped);
-// tile-major for injections and the adjoint (the state chunks of one
-// tile run on one XCD, so its tables come from that XCD's L2 after the
-// first chunk).
+// tile-major for injections (the state chunks of one tile run on one XCD, so
+// its tables come from that XCD's L2 after the first chunk) and grouped for
+// the adjoint, whose tables are the heaviest (20k buses x 512 states 227 us
+// tile-major, 207 grouped with 16 states per workgroup; 70k x 37 55.3 and
+// 53.4).  Grids numbered without regard to the network (scattered) take
+// state-major throughout: every XCD then works on one state at a time, whose
+// arrays fit in its L2 and serve its gathers, where the other orders gather
+// from the states of all resident workgroups at once (100k buses renumbered at
+// random, injections of 100 states: tile-major 924 us, grouped 577,
+// state-major with 8 states per workgroup 586, with one 315; adjoint of 60k x
+// 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).
 int work_order(const pf_grid *g, int kind) {
     switch (g->order) {
         case PF_ORDER_TILE_MAJOR:
@@ -935,9 +951,10 @@ int work_order(const pf_grid *g, int kind) {
         case PF_ORDER_GROUPED:
             return pf::WO_GROUPED;
         default:
-            if (!is_jacobian(kind)) return pf::WO_TILE;
+            if (g->scattered) return pf::WO_STATE;
+            if (kind == pf::K_EW_S || kind == pf::K_YB_S) return pf::WO_TILE;
             if (table_bytes(g, kind) >= (int64_t)1 << 19) return pf::WO_GROUPED;
-            return pf::WO_STATE;
+            return is_jacobian(kind) ? pf::WO_STATE : pf::WO_TILE;
     }
 }
 
@@ -952,13 +969,16 @@ int work_order(const pf_grid *g, int kind) {
 // most 8 for injections (small per-state outputs, so reusing the constants
 // pays); fewer when the tiles alone would leave part of one round of
 // resident workgroups empty (it then splits each tile's states into about
-// resident capacity / tiles chunks).  The adjoint takes exactly that split,
-// however many states it gives a workgroup: its record constants (both
-// ends' couplings) are the heaviest, and one round of workgroups that each
-// walk their share of the states measured fastest.
+// resident capacity / tiles chunks).  The adjoint takes that split up to 16
+// states: its record constants (both ends' couplings) are the heaviest.  On
+// scattered grids the states have to stay in step (see work_order): one state
+// per workgroup, two for Jacobian launches whose tables do not stay in L2
+// (S+J of 60k buses x 40 states 96 us at one, 84 at two; 6k x 60: 13.2, 14.7).
 int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (g->states_per_block > 0) return std::min<int32_t>(g->states_per_block, std::max(nstate, 1));
     if (nstate <= 1) return 1;
+    if (g->scattered && g->order == PF_ORDER_AUTO)
+        return is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1;
     const bool yb = kind == pf::K_YB_S || kind == pf::K_YB_SJ || kind == pf::K_YB_SJ_CSC;
     const int64_t nt = std::max<int64_t>(1, (int64_t)(yb ? g->ytiles : g->tiles).size());
     int per_cu = pf::resident_blocks_per_cu(kind, g->tile_items, g->has_parallel);
@@ -977,7 +997,7 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
         if (work_order(g, kind) == pf::WO_GROUPED) tb /= 8;
         return std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4);
     }
-    if (kind == pf::K_EW_VJP) return fill;
+    if (kind == pf::K_EW_VJP) return std::min(fill, 16);
     return std::min(fill, 8);
 }
 

@@ -109,3 +109,30 @@ def test_jacobian_states_per_workgroup_same_bits(tile, parallel):
             if want is None:
                 want = (p, q, j)
             assert all(torch.equal(a, b) for a, b in zip((p, q, j), want))
+
+
+# Grids numbered at random take other work orders than those numbered along
+# the network (2,500 buses: above the distance that counts as far; 900: below).
+@pytest.mark.parametrize("nb,nstate", [(900, 9), (2_500, 2), (2_500, 33), (7_001, 19)])
+def test_random_numbering_same_bits(nb, nstate):
+    import torch
+    _gpu.require_gpu()
+    g, _ = gridgen.relabel(gridgen.make_grid(nb, int(1.35 * nb), 0.15, case=9, grid=nb), 9, nb)
+    G = pf.Grid.from_grid(g)
+    pf.pf_ybus(G)
+    vm, va = (_gpu.to_dev(x) for x in gridgen.states(nb, nstate, case=9, grid=nb))
+    lp, lq = (_gpu.to_dev(x) for x in gridgen.adjoint_seeds(nb, nstate, case=9, grid=nb))
+    want = None
+    for sched in ((256, 0, pf.PF_ORDER_AUTO), (256, 1, pf.PF_ORDER_TILE_MAJOR), (128, 5, pf.PF_ORDER_GROUPED)):
+        G.set_schedule(*sched)
+        out = [torch.empty_like(vm) for _ in range(6)]
+        pf.pf_injections_elementwise(G, vm, va, out[0], out[1])
+        pf.pf_injections_ybus(G, vm, va, out[2], out[3])
+        pf.pf_injections_vjp(G, vm, va, lp, lq, out[4], out[5])
+        for method in METHODS:
+            out += [torch.empty_like(vm), torch.empty_like(vm),
+                    torch.empty((nstate, G.nnz_j), dtype=torch.float64, device="cuda:0")]
+            pf.pf_jacobian_values(G, method, vm, va, *out[-3:])
+        torch.cuda.synchronize()
+        want = want or out
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
