@@ -301,7 +301,8 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     automatic: at most 4 for Jacobian launches, 8 for
  *                     injections and 16 for the adjoint, fewer when the tiles
  *                     alone do not fill the GPU; with PF_ORDER_AUTO on grids
- *                     numbered without regard to the network 1 or 2)
+ *                     numbered without regard to the network 1 or 2, and 1
+ *                     on grids with rows of more than two tiles)
  *   order             order of the (tile, state chunk) work items over the
  *                     workgroups: PF_ORDER_TILE_MAJOR (the state chunks of
  *                     one tile are adjacent), PF_ORDER_STATE_MAJOR (the tiles
@@ -314,8 +315,10 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     (Jacobian launches and the adjoint: grouped, below
  *                     512 KB of tile tables state-major and tile-major;
  *                     injections: tile-major, so the state chunks of one
- *                     tile share an L2; all of them state-major on grids
- *                     numbered without regard to the network)
+ *                     tile share an L2, or grouped for many states or
+ *                     grids; all of them state-major on grids numbered
+ *                     without regard to the network or with rows of more
+ *                     than two tiles)
  * The initial schedule is tile_items 256 (with several grids per handle:
  * the smallest of 64, 128, 256 that holds the mean branch ends per grid,
  * since tiles never span grids), states_per_block 0, PF_ORDER_AUTO.

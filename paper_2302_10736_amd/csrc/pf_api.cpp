@@ -81,6 +81,7 @@ struct pf_grid {
 
     int32_t tile_items = 256, states_per_block = 0, order = PF_ORDER_AUTO;
     std::vector<pf::TileDesc> tiles, ytiles;  // element-wise and Ybus work tiles
+    bool long_rows = false;                   // some row takes three or more pieces of a tile (see work_order)
     bool scattered = false;                   // most branches join buses of distant numbers (see work_order)
     int32_t num_cus = 0;
     pf::DevLaneFill lanes{};  // gather sources and targets of the lane values
@@ -169,6 +170,8 @@ void build_tiles(pf_grid *g, int NT) {
         }
         close(g->ytiles, re);
     }
+    g->long_rows = false;
+    for (const pf::TileDesc &c : g->tiles) g->long_rows |= c.ne > 2 * NT;
 }
 
 // Lane tables of the packed tiles (tile size NT).  Positions inside the LDS
@@ -528,7 +531,10 @@ int pf_build_pattern(int32_t nb, int32_t nl, const int32_t *fbus, const int32_t 
         constexpr int32_t kFar = 512;
         int64_t far = 0;
         for (int64_t p = 0; p < g->nnz_y; ++p) far += std::abs(g->ycol[p] - g->slot_row[p]) > kFar;
-        g->scattered = 2 * far > g->nnz_y - nb;
+        int32_t largest = 0;
+        for (int32_t k = 0; k < ngrids; ++k) largest = std::max(largest, g->bus_off[k + 1] - g->bus_off[k]);
+        // Grids that fit in an XCD's share of the tiles are near each other.
+        g->scattered = 2 * far > g->nnz_y - nb && 4 * (int64_t)largest > nb;
         g->slot_item.push_back((int32_t)ni);
         g->has_parallel = g->nnz_y != ni;
         g->y_off.assign(ngrids + 1, 0);
@@ -931,7 +937,7 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 // rows, and later states can be read ahead, see ahead_of); state-major for
 // grids of tables below 512 KB, whose eighth would be fewer than eight tiles
 // (2,383 buses x 250 states, Ybus: 20.4 us state-major, 21.0 grouped);
-// tile-major for injections (the state chunks of one tile run on one XCD, so
+// tile-major for injections of few states (the state chunks of one tile run on one XCD, so
 // its tables come from that XCD's L2 after the first chunk) and grouped for
 // the adjoint, whose tables are the heaviest (20k buses x 512 states 227 us
 // tile-major, 207 grouped with 16 states per workgroup; 70k x 37 55.3 and
@@ -941,8 +947,15 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 // from the states of all resident workgroups at once (100k buses renumbered at
 // random, injections of 100 states: tile-major 924 us, grouped 577,
 // state-major with 8 states per workgroup 586, with one 315; adjoint of 60k x
-// 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).
-int work_order(const pf_grid *g, int kind) {
+// 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).  Long
+// rows take the same order with one state per workgroup: the workgroup of a
+// row walks its pieces one after another, so its states have to go to
+// different workgroups (20k buses with 20 hubs x 64 states: injections 83 us
+// tile-major with 8 states, 43; adjoint 307 and 67; S+J 77 grouped, 63).
+// Injections of many states or grids are grouped too (100k x 128 163 us
+// tile-major, 154 grouped; 43 grids of 728 to 4,838 buses x 70 200 and 162), of
+// fewer not (60k x 40 27.2 and 28.3).
+int work_order(const pf_grid *g, int kind, int32_t nstate) {
     switch (g->order) {
         case PF_ORDER_TILE_MAJOR:
             return pf::WO_TILE;
@@ -951,8 +964,9 @@ int work_order(const pf_grid *g, int kind) {
         case PF_ORDER_GROUPED:
             return pf::WO_GROUPED;
         default:
-            if (g->scattered) return pf::WO_STATE;
-            if (kind == pf::K_EW_S || kind == pf::K_YB_S) return pf::WO_TILE;
+            if (g->scattered || g->long_rows) return pf::WO_STATE;
+            if (kind == pf::K_EW_S || kind == pf::K_YB_S)
+                return table_bytes(g, kind) >= (int64_t)1 << 19 && (nstate >= 64 || g->ngrids > 1) ? pf::WO_GROUPED : pf::WO_TILE;
             if (table_bytes(g, kind) >= (int64_t)1 << 19) return pf::WO_GROUPED;
             return is_jacobian(kind) ? pf::WO_STATE : pf::WO_TILE;
     }
@@ -977,6 +991,7 @@ int work_order(const pf_grid *g, int kind) {
 int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (g->states_per_block > 0) return std::min<int32_t>(g->states_per_block, std::max(nstate, 1));
     if (nstate <= 1) return 1;
+    if (g->long_rows && g->order == PF_ORDER_AUTO) return 1;
     if (g->scattered && g->order == PF_ORDER_AUTO)
         return is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1;
     const bool yb = kind == pf::K_YB_S || kind == pf::K_YB_SJ || kind == pf::K_YB_SJ_CSC;
@@ -994,7 +1009,7 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
         // (64 grids of 1k to 80k buses x 4 states: 170 us at two, 158 at
         // four; 300k buses x 16: 153 and 146).
         int64_t tb = table_bytes(g, kind);
-        if (work_order(g, kind) == pf::WO_GROUPED) tb /= 8;
+        if (work_order(g, kind, nstate) == pf::WO_GROUPED) tb /= 8;
         return std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4);
     }
     if (kind == pf::K_EW_VJP) return std::min(fill, 16);
@@ -1009,10 +1024,12 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
 // an XCD's 32 compute units) has in flight.  The states read ahead have to
 // stay in the XCD's L2 until they are used: 3 of its 4 MB.
 int ahead_of(const pf_grid *g, const pf::Launch &L) {
-    if (L.nstate < 10) return 0;
     if (!is_jacobian(L.kind) || L.phasor != pf::PH_FLY || L.states_per_block != 1 || L.order != pf::WO_GROUPED) return 0;
     const bool yb = L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
     const int64_t walk = ((int64_t)(yb ? g->ytiles : g->tiles).size() + 7) / 8;  // tiles per XCD and state
+    // Inputs that fit in half of the 256 MB memory-side cache may be there, and
+    // then reading ahead only costs (100k x 32, 51 MB: 80 us without, 88 with).
+    if ((int64_t)L.nstate * g->nb * 16 < (int64_t)128 << 20) return 0;
     const int64_t burst = 8, dist = 256 / walk + 1;
     if (L.nstate < dist + burst || walk < 8) return 0;  // fewer states: nothing to gain (40k buses x 8: 1 % lost)
     if ((burst + dist) * 2 * (int64_t)g->nb > (int64_t)3 << 20) return 0;  // 16 bytes a bus, an eighth of the buses
@@ -1039,7 +1056,7 @@ int run(const pf_grid *g, pf::Launch &L, void *stream) {
     L.tile_items = g->tile_items;
     L.has_parallel = g->has_parallel;
     L.states_per_block = auto_states_per_block(g, L.kind, L.nstate);
-    L.order = work_order(g, L.kind);
+    L.order = work_order(g, L.kind, L.nstate);
     L.ahead = ahead_of(g, L);
     if (L.nstate == 0) return PF_OK;
     int cur = -1;
