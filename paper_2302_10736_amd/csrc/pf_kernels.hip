@@ -1723,16 +1723,27 @@ __global__ void k_ca_branch(DevTwoPhase d, int nstate, int64_t nnz_j, const doub
 
 // Jacobian values into another pattern (Algorithm 2's in-place copy by
 // precomputed indices): one thread per J entry reads its target position
-// once and copies the entry of every state.  Positions outside the target
-// are skipped, so a wrong map cannot write out of bounds.
-__global__ void k_jscatter(int32_t nstate, int64_t nnz_j, const double *__restrict__ jval,
-                           const int32_t *__restrict__ map, int64_t out_nnz, double *__restrict__ out) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// once and copies the entry of spb states.  Positions outside the target
+// are skipped, so a wrong map cannot write out of bounds.  Bound by the
+// memory's writes: runs of entries start and end anywhere in a 128-byte line,
+// and the target's other entries lie between them.  So neighbouring entries
+// stay on one XCD and the stores are plain: its L2 joins the parts of a line,
+// where streaming stores wrote each by itself.  40k buses x 8 states (576k
+// entries a state): 19 -> 16 us; streaming stores in this order 18, two states
+// per thread 17, eight 17.
+__global__ void __launch_bounds__(256)
+    k_jscatter(int32_t nstate, int32_t spb, int64_t nnz_j, const double *__restrict__ jval,
+               const int32_t *__restrict__ map, int64_t out_nnz, double *__restrict__ out) {
+    const int nkb = (int)((nnz_j + 255) / 256);
+    const int w = work_index(gridDim.x);
+    const int c = w / nkb;
+    const int64_t k = (int64_t)(w - c * nkb) * 256 + threadIdx.x;
     if (k >= nnz_j) return;
     const int32_t m = map[k];
     if (m < 0 || m >= out_nnz) return;
-    for (int32_t s = blockIdx.y; s < nstate; s += gridDim.y)
-        st_out(out + (size_t)s * (size_t)out_nnz + m, jval[(size_t)s * (size_t)nnz_j + k]);
+    const int64_t se = min((int64_t)nstate, ((int64_t)c + 1) * spb);
+    for (int64_t s = (int64_t)c * spb; s < se; ++s)
+        out[(size_t)s * (size_t)out_nnz + m] = jval[(size_t)s * (size_t)nnz_j + k];
 }
 
 // Lane values: copies of the record constants (element-wise) or Ybus values
@@ -2055,10 +2066,11 @@ hipError_t launch_phasor(int32_t layout, int64_t n, const double *vm, const doub
 hipError_t launch_jscatter(int32_t nstate, int64_t nnz_j, const double *jval, const int32_t *map, int64_t out_nnz,
                            double *out, hipStream_t stream) {
     if (nstate == 0 || nnz_j == 0) return hipSuccess;
-    const int64_t blocks = (nnz_j + 255) / 256;
-    if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)blocks, (unsigned)std::min<int32_t>(nstate, 65535));
-    hipLaunchKernelGGL(k_jscatter, grid, dim3(256), 0, stream, nstate, nnz_j, jval, map, out_nnz, out);
+    const int64_t nkb = (nnz_j + 255) / 256;
+    const int64_t chunks = std::max<int64_t>(1, ((int64_t)1 << 30) / nkb);  // at most: the grid's limit
+    const int32_t spb = (int32_t)std::max<int64_t>(4, (nstate + chunks - 1) / chunks);
+    const int64_t blocks = (nkb * ((nstate + (int64_t)spb - 1) / spb) + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL(k_jscatter, dim3((unsigned)blocks), dim3(256), 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
     return hipGetLastError();
 }
 

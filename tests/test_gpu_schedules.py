@@ -133,3 +133,24 @@ def test_random_numbering_same_bits(nb, nstate):
         torch.cuda.synchronize()
         want = want or out
         assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
+# States below, at and past a thread's four; positions outside the target are
+# skipped and entries that J does not cover stay as they are.
+@pytest.mark.parametrize("nb,nstate", [(3, 1), (40, 4), (41, 5), (700, 3), (701, 13)])
+def test_scatter_states_and_skips(nb, nstate):
+    import torch
+    _gpu.require_gpu()
+    G = pf.Grid.from_grid(gridgen.make_grid(nb, max(nb - 1, int(1.3 * nb)), 0.15, case=9, grid=nb))
+    rng = np.random.default_rng(nb)
+    out_nnz = G.nnz_j + 37
+    pos = rng.permutation(out_nnz)[:G.nnz_j].astype(np.int32)
+    pos[::11] = -1
+    pos[5::13] = out_nnz
+    jval = rng.standard_normal((nstate, G.nnz_j))
+    want = np.full((nstate, out_nnz), -7.0)
+    ok = (pos >= 0) & (pos < out_nnz)
+    want[:, pos[ok]] = jval[:, ok]
+    out = torch.full((nstate, out_nnz), -7.0, dtype=torch.float64, device="cuda:0")
+    pf.pf_jacobian_scatter(G, _gpu.to_dev(jval), torch.as_tensor(pos, device="cuda:0"), out)
+    assert np.array_equal(out.cpu().numpy(), want)
