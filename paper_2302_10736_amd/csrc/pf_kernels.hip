@@ -19,9 +19,11 @@
 //      stores: a tile's rows are two contiguous ranges of the CSR value
 //      array (the P rows and the Q rows).
 // No atomics; every sum has a fixed order set by the pattern, so results do
-// not depend on the tile size or on the states per workgroup.  LDS buffers
-// alternate between consecutive states (two barriers per state), and the
-// gathers of the next state are issued before the current one is reduced.
+// not depend on the tile size or on the states per workgroup.  Injections and
+// the adjoint of several states per workgroup load the next state while one is
+// reduced; launches with J take one state after another, with more workgroups
+// per compute unit instead, or one state per workgroup and, in the grouped
+// order, the states of later workgroups read ahead in bursts (read_ahead).
 // A row with more than NT records is a tile of its own, walked in pieces of
 // NT records: the piece's 16-term chunks are summed in parallel and folded
 // in order by one thread, so its sums keep the packed path's order.  The
@@ -1502,21 +1504,25 @@ __device__ __forceinline__ void branch_ends(const BranchConsts &c, double phi, d
     t = branch_end(vk, vh, -sn, cs, c.At, c.Ct, c.G, c.B);
 }
 
-// Branch l of the baselines.  PRE reads the precomputed constants (56 bytes
-// per branch with the shift) instead of deriving them from the parameters (40
+// The constants of branch l.  PRE reads the precomputed ones (56 bytes per
+// branch with the shift) instead of deriving them from the parameters (40
 // bytes); the values are the same.
+template <bool PRE>
+__device__ __forceinline__ BranchConsts load_consts(const DevTwoPhase &d, int l) {
+    if constexpr (PRE) {
+        const size_t n = (size_t)d.nl;
+        return {d.bc[l], d.bc[n + l], d.bc[2 * n + l], d.bc[3 * n + l], d.bc[4 * n + l], d.bc[5 * n + l]};
+    } else {
+        return branch_consts(d.r[l], d.x[l], d.b[l], d.tap[l]);
+    }
+}
+
+// Branch l of the baselines at one state.
 template <bool PRE = false>
 __device__ __forceinline__ void branch_ends(const DevTwoPhase &d, int l, const double *vm, const double *va,
                                             EndVals &f, EndVals &t) {
     const int h = d.br_from[l], k = d.br_to[l];
-    BranchConsts c;
-    if constexpr (PRE) {
-        const size_t n = (size_t)d.nl;
-        c = {d.bc[l], d.bc[n + l], d.bc[2 * n + l], d.bc[3 * n + l], d.bc[4 * n + l], d.bc[5 * n + l]};
-    } else {
-        c = branch_consts(d.r[l], d.x[l], d.b[l], d.tap[l]);
-    }
-    branch_ends(c, d.shift[l], vm[h], va[h], vm[k], va[k], f, t);
+    branch_ends(load_consts<PRE>(d, l), d.shift[l], vm[h], va[h], vm[k], va[k], f, t);
 }
 
 // Plain stores: the reduction kernel reads the scratch right after, from cache.
@@ -1552,34 +1558,39 @@ __global__ void k_tp_branch(DevTwoPhase d, const double *__restrict__ vm, const 
 // up three whole lines; the workgroups of neighbouring branches run on one
 // XCD.  41,115 branches x 24 states: 51.8 -> 32.1 us (5.3 TB/s; whole lines
 // without the XCD order 46.4, the order alone 52.2, 256-branch workgroups
-// aligned as a whole 44.5, two or three states per lane 34.6 and 35.3).
-constexpr int kFlowWave = 48, kFlowBack = 16, kFlowBlock = 4 * kFlowWave;
-
-template <bool WITH_J>
+// aligned as a whole 44.5, two or three states per lane 34.6 and 35.3).  Rows
+// that all start on a line (BACK = 0) need no overlap.  A single state (MANY =
+// false) is one short round of workgroups, bound by its loads: neither the
+// overlap nor the XCD order pays there (100k buses, 130k branches cold 7.3 us
+// without, 8.9 with the order and precomputed constants), and the constants are
+// derived from the parameters, 16 bytes a branch less to read.
+template <bool WITH_J, int BACK, bool MANY>
 __global__ void __launch_bounds__(256)
     k_flows(DevTwoPhase d, int nstate, int nsb, const double *__restrict__ vm, const double *__restrict__ va,
             double *__restrict__ pf, double *__restrict__ qf, double *__restrict__ pt, double *__restrict__ qt,
             double *__restrict__ jac) {
-    const int nlb = (d.nl + kFlowBlock + kFlowBack - 1) / kFlowBlock;
-    const int w = work_index(gridDim.x);
-    const int s0 = w / nlb, lb = w - s0 * nlb;
+    constexpr int WAVE = 64 - BACK, BLOCK = 4 * WAVE;
+    const int nlb = (d.nl + BLOCK + BACK - 1) / BLOCK;
+    const int w = MANY ? work_index(gridDim.x) : (int)blockIdx.x;
+    const int s0 = MANY ? w / nlb : 0, lb = MANY ? w - s0 * nlb : w;
     if (s0 >= nsb) return;
-    const int out0 = lb * kFlowBlock + (int)(threadIdx.x / 64) * kFlowWave;  // the wave's outputs, before the row's shift
-    const int lr = out0 - kFlowBack + (int)(threadIdx.x & 63);
+    const int out0 = lb * BLOCK + (int)(threadIdx.x / 64) * WAVE;  // the wave's outputs, before the row's shift
+    const int lr = out0 - BACK + (int)(threadIdx.x & 63);
     const bool in = lr >= 0 && lr < d.nl;
     const int l = min(max(lr, 0), d.nl - 1);
     const int h = d.br_from[l], k = d.br_to[l];
     const size_t n = (size_t)d.nl;
-    const BranchConsts c = {d.bc[l], d.bc[n + l], d.bc[2 * n + l], d.bc[3 * n + l], d.bc[4 * n + l], d.bc[5 * n + l]};
+    const BranchConsts c = load_consts<MANY>(d, l);
     const double phi = d.shift[l];
     for (int s = s0; s < nstate; s += nsb) {
         const double *vms = vm + (size_t)s * d.nb, *vas = va + (size_t)s * d.nb;
         EndVals f, t;
         branch_ends(c, phi, vms[h], vas[h], vms[k], vas[k], f, t);
         auto put = [&](double *row, double v) {
-            const int first = out0 - ((int)((uintptr_t)(row + out0) >> 3) & 15);  // where a line starts
-            if (in && lr >= first && lr < first + kFlowWave) st_out(row + lr, v);
+            const int first = BACK ? out0 - ((int)((uintptr_t)(row + out0) >> 3) & 15) : out0;  // where a line starts
+            if (BACK ? in && lr >= first && lr < first + WAVE : in) st_out(row + lr, v);
         };
+        if (!BACK && !in) continue;
         put(pf + s * n, f.p);
         put(qf + s * n, f.q);
         put(pt + s * n, t.p);
@@ -1726,24 +1737,36 @@ __global__ void k_ca_branch(DevTwoPhase d, int nstate, int64_t nnz_j, const doub
 // once and copies the entry of spb states.  Positions outside the target
 // are skipped, so a wrong map cannot write out of bounds.  Bound by the
 // memory's writes: runs of entries start and end anywhere in a 128-byte line,
-// and the target's other entries lie between them.  So neighbouring entries
-// stay on one XCD and the stores are plain: its L2 joins the parts of a line,
-// where streaming stores wrote each by itself.  40k buses x 8 states (576k
-// entries a state): 19 -> 16 us; streaming stores in this order 18, two states
-// per thread 17, eight 17.
+// and the target's other entries lie between them.  So with four states or more
+// (MANY) neighbouring entries stay on one XCD, and for targets of at most 48 MB
+// (PLAIN) the stores are plain: its L2 joins the parts of a line, where
+// streaming stores write each by itself.  40k buses x 8 states (37 MB): 19 us
+// before, 16 plain, 18 streaming; two or eight states per thread 17.  Larger
+// targets would fill the memory-side cache and push the values still to be read
+// out of it (68k x 8, 69 MB: 35 us before, 41 plain, 30 streaming).  A single
+// state is one short round of workgroups: 100k buses x 1, cold, 7.2 us, 9.1 in
+// the XCD order and 10.1 with plain stores too.
+template <bool MANY, bool PLAIN>
 __global__ void __launch_bounds__(256)
     k_jscatter(int32_t nstate, int32_t spb, int64_t nnz_j, const double *__restrict__ jval,
                const int32_t *__restrict__ map, int64_t out_nnz, double *__restrict__ out) {
     const int nkb = (int)((nnz_j + 255) / 256);
-    const int w = work_index(gridDim.x);
-    const int c = w / nkb;
-    const int64_t k = (int64_t)(w - c * nkb) * 256 + threadIdx.x;
+    const int w = MANY ? work_index(gridDim.x) : (int)blockIdx.x;
+    const int c = MANY ? w / nkb : (int)blockIdx.y;
+    const int64_t k = (int64_t)(MANY ? w - c * nkb : w) * 256 + threadIdx.x;
     if (k >= nnz_j) return;
     const int32_t m = map[k];
     if (m < 0 || m >= out_nnz) return;
+    if constexpr (!MANY) {  // one state per workgroup
+        st_out(out + (size_t)c * (size_t)out_nnz + m, jval[(size_t)c * (size_t)nnz_j + k]);
+        return;
+    }
     const int64_t se = min((int64_t)nstate, ((int64_t)c + 1) * spb);
     for (int64_t s = (int64_t)c * spb; s < se; ++s)
-        out[(size_t)s * (size_t)out_nnz + m] = jval[(size_t)s * (size_t)nnz_j + k];
+        if constexpr (PLAIN)
+            out[(size_t)s * (size_t)out_nnz + m] = jval[(size_t)s * (size_t)nnz_j + k];
+        else
+            st_out(out + (size_t)s * (size_t)out_nnz + m, jval[(size_t)s * (size_t)nnz_j + k]);
 }
 
 // Lane values: copies of the record constants (element-wise) or Ybus values
@@ -2036,18 +2059,30 @@ hipError_t launch_copy_add(const DevTwoPhase &d, int32_t nstate, int64_t nnz_j, 
     return hipGetLastError();
 }
 
-hipError_t launch_flows(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
-                        double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
-    if (d.nl == 0 || nstate == 0) return hipSuccess;
+template <int BACK, bool MANY>
+hipError_t launch_flows_as(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
+                           double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
     // One state per workgroup while the grid allows it.
-    const int64_t nlb = ((int64_t)d.nl + kFlowBlock + kFlowBack - 1) / kFlowBlock;
+    constexpr int BLOCK = 4 * (64 - BACK);
+    const int64_t nlb = ((int64_t)d.nl + BLOCK + BACK - 1) / BLOCK;
     const int nsb = (int)std::min<int64_t>(nstate, std::max<int64_t>(1, ((int64_t)1 << 30) / nlb));
     const dim3 grid((unsigned)((nlb * nsb + kXcds - 1) / kXcds * kXcds));
     if (jac)
-        hipLaunchKernelGGL(k_flows<true>, grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
+        hipLaunchKernelGGL((k_flows<true, BACK, MANY>), grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
     else
-        hipLaunchKernelGGL(k_flows<false>, grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
+        hipLaunchKernelGGL((k_flows<false, BACK, MANY>), grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
     return hipGetLastError();
+}
+
+hipError_t launch_flows(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
+                        double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
+    if (d.nl == 0 || nstate == 0) return hipSuccess;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(pf) | reinterpret_cast<uintptr_t>(qf) | reinterpret_cast<uintptr_t>(pt) |
+                         reinterpret_cast<uintptr_t>(qt) | reinterpret_cast<uintptr_t>(jac);
+    const bool lines = at % 128 == 0 && d.nl % 16 == 0;  // every row starts on a line
+    if (nstate == 1) return launch_flows_as<0, false>(d, nstate, vm, va, pf, qf, pt, qt, jac, stream);
+    return lines ? launch_flows_as<0, true>(d, nstate, vm, va, pf, qf, pt, qt, jac, stream)
+                 : launch_flows_as<16, true>(d, nstate, vm, va, pf, qf, pt, qt, jac, stream);
 }
 
 hipError_t launch_phasor(int32_t layout, int64_t n, const double *vm, const double *va, double *ph, hipStream_t stream) {
@@ -2068,9 +2103,17 @@ hipError_t launch_jscatter(int32_t nstate, int64_t nnz_j, const double *jval, co
     if (nstate == 0 || nnz_j == 0) return hipSuccess;
     const int64_t nkb = (nnz_j + 255) / 256;
     const int64_t chunks = std::max<int64_t>(1, ((int64_t)1 << 30) / nkb);  // at most: the grid's limit
-    const int32_t spb = (int32_t)std::max<int64_t>(4, (nstate + chunks - 1) / chunks);
+    const bool many = nstate >= 4;
+    const int32_t spb = (int32_t)std::max<int64_t>(many ? 4 : 1, (nstate + chunks - 1) / chunks);
     const int64_t blocks = (nkb * ((nstate + (int64_t)spb - 1) / spb) + kXcds - 1) / kXcds * kXcds;
-    hipLaunchKernelGGL(k_jscatter, dim3((unsigned)blocks), dim3(256), 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
+    const dim3 grid((unsigned)blocks), block(256);
+    if (many && (int64_t)nstate * out_nnz <= ((int64_t)48 << 20) / 8)
+        hipLaunchKernelGGL((k_jscatter<true, true>), grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
+    else if (many)
+        hipLaunchKernelGGL((k_jscatter<true, false>), grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
+    else
+        hipLaunchKernelGGL((k_jscatter<false, false>), dim3((unsigned)nkb, (unsigned)nstate), block, 0, stream, nstate, spb,
+                           nnz_j, jval, map, out_nnz, out);
     return hipGetLastError();
 }
 
