@@ -991,11 +991,13 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
 int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (g->states_per_block > 0) return std::min<int32_t>(g->states_per_block, std::max(nstate, 1));
     if (nstate <= 1) return 1;
-    if (g->long_rows && g->order == PF_ORDER_AUTO) return 1;
-    if (g->scattered && g->order == PF_ORDER_AUTO)
-        return is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1;
     const bool yb = kind == pf::K_YB_S || kind == pf::K_YB_SJ || kind == pf::K_YB_SJ_CSC;
     const int64_t nt = std::max<int64_t>(1, (int64_t)(yb ? g->ytiles : g->tiles).size());
+    // A launch holds less than 2^32 threads: at most 2^22 workgroups.
+    const int least = (int)std::min<int64_t>(nstate, (nt * nstate + (1 << 22) - 1) >> 22);
+    if (g->long_rows && g->order == PF_ORDER_AUTO) return least;
+    if (g->scattered && g->order == PF_ORDER_AUTO)
+        return std::max(least, is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1);
     int per_cu = pf::resident_blocks_per_cu(kind, g->tile_items, g->has_parallel);
     if (per_cu <= 0) per_cu = 4;
     const int64_t capacity = (int64_t)std::max(g->num_cus, 1) * per_cu;
@@ -1010,10 +1012,10 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
         // four; 300k buses x 16: 153 and 146).
         int64_t tb = table_bytes(g, kind);
         if (work_order(g, kind, nstate) == pf::WO_GROUPED) tb /= 8;
-        return std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4);
+        return std::max(least, std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4));
     }
-    if (kind == pf::K_EW_VJP) return std::min(fill, 16);
-    return std::min(fill, 8);
+    if (kind == pf::K_EW_VJP) return std::max(least, std::min(fill, 16));
+    return std::max(least, std::min(fill, 8));
 }
 
 // Read-ahead of a launch (read_ahead in pf_kernels.hip): bursts of 8 states,

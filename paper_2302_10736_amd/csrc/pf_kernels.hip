@@ -29,8 +29,7 @@
 // in order by one thread, so its sums keep the packed path's order.  The
 // work items (tile, chunk of states) map to workgroups XCD by XCD in one of
 // three orders (tile-major, state-major, grouped; see work_item).  The
-// baselines further
-// down (the two-phase and copy-add methods, branch flows) use one thread
+// baselines further down (the two-phase and copy-add methods, branch flows) use one thread
 // per branch instead.
 //
 // Element-wise records
@@ -2062,10 +2061,10 @@ hipError_t launch_copy_add(const DevTwoPhase &d, int32_t nstate, int64_t nnz_j, 
 template <int BACK, bool MANY>
 hipError_t launch_flows_as(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
                            double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
-    // One state per workgroup while the grid allows it.
+    // One state per workgroup while the launch holds less than 2^32 threads.
     constexpr int BLOCK = 4 * (64 - BACK);
     const int64_t nlb = ((int64_t)d.nl + BLOCK + BACK - 1) / BLOCK;
-    const int nsb = (int)std::min<int64_t>(nstate, std::max<int64_t>(1, ((int64_t)1 << 30) / nlb));
+    const int nsb = (int)std::min<int64_t>(nstate, std::max<int64_t>(1, ((int64_t)1 << 23) / nlb));
     const dim3 grid((unsigned)((nlb * nsb + kXcds - 1) / kXcds * kXcds));
     if (jac)
         hipLaunchKernelGGL((k_flows<true, BACK, MANY>), grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
@@ -2102,7 +2101,7 @@ hipError_t launch_jscatter(int32_t nstate, int64_t nnz_j, const double *jval, co
                            double *out, hipStream_t stream) {
     if (nstate == 0 || nnz_j == 0) return hipSuccess;
     const int64_t nkb = (nnz_j + 255) / 256;
-    const int64_t chunks = std::max<int64_t>(1, ((int64_t)1 << 30) / nkb);  // at most: the grid's limit
+    const int64_t chunks = std::max<int64_t>(1, ((int64_t)1 << 23) / nkb);  // at most: the grid's limit
     const bool many = nstate >= 4;
     const int32_t spb = (int32_t)std::max<int64_t>(many ? 4 : 1, (nstate + chunks - 1) / chunks);
     const int64_t blocks = (nkb * ((nstate + (int64_t)spb - 1) / spb) + kXcds - 1) / kXcds * kXcds;

@@ -81,6 +81,23 @@ def test_flow_rows_any_alignment(nl, nstate, off):
         assert _gpu.rel_err(got[4][s], np.asarray(oracle.branch_flow_jac(g, vm[s], va[s])).reshape(got[4][s].shape)) <= _gpu.TOL
 
 
+# More states than a launch of less than 2^32 threads holds workgroups of 256:
+# every state of a repeating sequence of seven has the flows of its first turn.
+def test_flows_of_many_states():
+    import torch
+    _gpu.require_gpu()
+    g = gridgen.make_grid(2, 1, 0.0, case=9)
+    G = pf.Grid.from_grid(g)
+    nstate = (1 << 24) + 5
+    vm, va = (_gpu.to_dev(x).repeat(nstate // 7 + 1, 1)[:nstate].contiguous() for x in gridgen.states(2, 7, case=9))
+    outs = [torch.full((nstate, g.nl), -7.0, dtype=torch.float64, device="cuda:0") for _ in range(4)]
+    pf.pf_branch_flows(G, vm, va, *outs)
+    few = [torch.empty((7, g.nl), dtype=torch.float64, device="cuda:0") for _ in range(4)]
+    pf.pf_branch_flows(G, vm[:7], va[:7], *few)
+    for o, f in zip(outs, few):
+        assert torch.equal(o, f.repeat(nstate // 7 + 1, 1)[:nstate])
+
+
 # States per workgroup of the Jacobian loop: one, a few, more than there are.
 @pytest.mark.parametrize("tile", [64, 256, 512])
 @pytest.mark.parametrize("parallel", [False, True])
