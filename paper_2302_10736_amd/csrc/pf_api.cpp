@@ -1014,7 +1014,14 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
         if (work_order(g, kind, nstate) == pf::WO_GROUPED) tb /= 8;
         return std::max(least, std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4));
     }
-    if (kind == pf::K_EW_VJP) return std::max(least, std::min(fill, 16));
+    if (kind == pf::K_EW_VJP) {
+        // Where one workgroup per tile fills the chip (seven eighths of it) it
+        // walks up to 32 states, the heaviest tables read once (100k buses x
+        // 32: 50.0 us at 16, 48.6 at 32); else shorter ones even out the rounds
+        // (82k x 20: 28.6 at 16, 32.2 at 20; 14k x 300: 83 at 16, 93 at 32).
+        const bool full = nt <= capacity && 8 * nt >= 7 * capacity;
+        return std::max(least, std::min(fill, full ? 32 : 16));
+    }
     return std::max(least, std::min(fill, 8));
 }
 
