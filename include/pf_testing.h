@@ -9,6 +9,8 @@
 
 #include <stdint.h>
 
+#include "pf.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -30,6 +32,14 @@ int pf_stream_copy(const double *src, double *dst, int64_t n, void *stream);
  * existing handle as it was.  n = 0 clears the count.  Process-wide.
  * Errors: PF_EINVAL for n < 0. */
 int pf_debug_fail_allocs(int32_t n);
+
+/* The launch that the evaluation call for (op, method) (as in pf_op) makes for
+ * nstate states under the handle's present schedule; nothing is launched.
+ * plan (5 values): states per workgroup, work order (PF_ORDER_TILE_MAJOR,
+ * PF_ORDER_STATE_MAJOR or PF_ORDER_GROUPED), 1 if later states are read ahead
+ * (else 0), workgroups, threads per workgroup.  On a PF_BUILD_HOST_ONLY handle
+ * a device of 256 compute units is assumed.  Errors: PF_EINVAL. */
+int pf_debug_launch(const pf_grid *g, int32_t op, int32_t method, int32_t nstate, int64_t *plan);
 
 #ifdef __cplusplus
 }

@@ -63,9 +63,17 @@ struct Arena {
     }
 };
 
+// What a tile size decides on the host.  One object, so that a schedule change
+// that fails can put all of it back.
+struct Tiling {
+    int32_t tile_items = 256;
+    std::vector<pf::TileDesc> tiles, ytiles;  // element-wise and Ybus work tiles
+    bool long_rows = false;                   // some row takes three or more pieces of a tile (see work_order)
+};
+
 }  // namespace
 
-struct pf_grid {
+struct pf_grid : Tiling {
     int32_t nb = 0, nl = 0, ngrids = 1;
     int64_t nnz_y = 0, nitems = 0;
     bool has_parallel = false;
@@ -79,11 +87,9 @@ struct pf_grid {
     std::vector<int32_t> irow, nbr, slot, item_br;
     std::vector<int32_t> slot_row, slot_item;
 
-    int32_t tile_items = 256, states_per_block = 0, order = PF_ORDER_AUTO;
-    std::vector<pf::TileDesc> tiles, ytiles;  // element-wise and Ybus work tiles
-    bool long_rows = false;                   // some row takes three or more pieces of a tile (see work_order)
+    int32_t states_per_block = 0, order = PF_ORDER_AUTO;
     bool scattered = false;                   // most branches join buses of distant numbers (see work_order)
-    int32_t num_cus = 0;
+    int32_t num_cus = 256;  // of the handle's device
     pf::DevLaneFill lanes{};  // gather sources and targets of the lane values
     pf::DevTwoPhase tp{};     // two-phase element-wise tables and scratch (inside dmem)
 
@@ -867,14 +873,12 @@ int pf_set_schedule(pf_grid *g, int32_t tile_items, int32_t states_per_block, in
         return fail(PF_EINVAL, "unknown order");
     if (tile_items != g->tile_items) {
         // new tiles on the host and device; on failure the old ones stay
-        std::vector<pf::TileDesc> old_t, old_yt;
+        Tiling old;
         try {
-            old_t = g->tiles;
-            old_yt = g->ytiles;
+            old = *g;
         } catch (const std::bad_alloc &) {
             return fail(PF_ENOMEM, "host allocation failed");
         }
-        const int32_t old_items = g->tile_items;
         int st = PF_OK;
         try {
             g->tile_items = tile_items;
@@ -884,9 +888,7 @@ int pf_set_schedule(pf_grid *g, int32_t tile_items, int32_t states_per_block, in
             st = fail(PF_ENOMEM, "host allocation failed");
         }
         if (st != PF_OK) {
-            g->tiles.swap(old_t);
-            g->ytiles.swap(old_yt);
-            g->tile_items = old_items;
+            static_cast<Tiling &>(*g) = std::move(old);
             return st;
         }
     }
@@ -1061,13 +1063,18 @@ int run_two_phase(const pf_grid *g, int32_t nstate, const double *vm, const doub
     return PF_OK;
 }
 
-int run(const pf_grid *g, pf::Launch &L, void *stream) {
+// The launch shape of L.nstate states of L.kind.
+void plan(const pf_grid *g, pf::Launch &L) {
     L.tile_items = g->tile_items;
     L.has_parallel = g->has_parallel;
     L.states_per_block = auto_states_per_block(g, L.kind, L.nstate);
     L.order = work_order(g, L.kind, L.nstate);
     L.ahead = ahead_of(g, L);
+}
+
+int run(const pf_grid *g, pf::Launch &L, void *stream) {
     if (L.nstate == 0) return PF_OK;
+    plan(g, L);
     int cur = -1;
     hipError_t e = hipGetDevice(&cur);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
@@ -1366,6 +1373,27 @@ int record_op(const pf_grid *g, const pf_op &o, void *stream) {
 }  // namespace
 
 extern "C" {
+
+int pf_debug_launch(const pf_grid *g, int32_t op, int32_t method, int32_t nstate, int64_t *plan_out) {
+    g_err.clear();
+    if (!g || !plan_out) return fail(PF_EINVAL, "NULL handle or output");
+    if (nstate < 1) return fail(PF_EINVAL, "nstate must be >= 1");
+    if (op != PF_OP_INJECTIONS && op != PF_OP_JACOBIAN && op != PF_OP_VJP) return fail(PF_EINVAL, "unknown op");
+    pf_op o{};
+    o.op = op;
+    o.method = method;
+    pf::Launch L{};
+    L.kind = op_kind(o);
+    L.nstate = nstate;
+    plan(g, L);
+    const bool yb = L.kind == pf::K_YB_S || L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
+    plan_out[0] = L.states_per_block;
+    plan_out[1] = L.order == pf::WO_TILE ? PF_ORDER_TILE_MAJOR : L.order == pf::WO_STATE ? PF_ORDER_STATE_MAJOR : PF_ORDER_GROUPED;
+    plan_out[2] = L.ahead != 0;
+    plan_out[3] = pf::eval_blocks(L, (int64_t)(yb ? g->ytiles : g->tiles).size());
+    plan_out[4] = L.tile_items;
+    return PF_OK;
+}
 
 int pf_graph_create(const pf_grid *g, const pf_op *ops, int32_t nops, pf_graph **out) {
     g_err.clear();

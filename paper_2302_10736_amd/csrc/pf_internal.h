@@ -153,6 +153,15 @@ struct Launch {
     const double *ph;  // stored phasors (layout of launch_phasor)
 };
 
+constexpr int kXcds = 8;
+
+// Workgroups of a launch over ntiles tiles (see work_item in pf_kernels.hip).
+inline int64_t eval_blocks(const Launch &L, int64_t ntiles) {
+    const int64_t nchunk = ((int64_t)L.nstate + L.states_per_block - 1) / L.states_per_block;
+    return L.order == WO_GROUPED ? kXcds * ((ntiles + kXcds - 1) / kXcds) * nchunk
+                                 : (ntiles * nchunk + kXcds - 1) / kXcds * kXcds;
+}
+
 hipError_t launch_eval(const DevGrid &g, const Launch &L, hipStream_t stream);
 // Workgroups of the evaluation kernel for (kind, tile_items, has_parallel)
 // that one compute unit holds at once (0 if unknown).

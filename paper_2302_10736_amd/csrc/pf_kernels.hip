@@ -74,8 +74,6 @@ __constant__ SinCosCoef g_sincos = kSinCosTaylor;
 
 namespace {
 
-constexpr int kXcds = 8;
-
 // sincos_rad, with its reduction and quadrant fix-up skipped when every lane
 // of the wave has quadrant count 0 (angle differences within about pi/4, the
 // usual case in power-flow states).  Same bits either way (pf_math.h), so a
@@ -1855,11 +1853,9 @@ void launch_ew(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb
 template <int NT, bool ONE>
 hipError_t launch_nt(const DevGrid &g, const Launch &L, hipStream_t st) {
     const int spb = L.states_per_block;
-    const int nchunk = (L.nstate + spb - 1) / spb;
+    const int nchunk = (int)(((int64_t)L.nstate + spb - 1) / spb);
     const bool yb = L.kind == K_YB_S || L.kind == K_YB_SJ || L.kind == K_YB_SJ_CSC;
-    const int64_t ntl = yb ? g.nytiles : g.ntiles;
-    const int64_t blocks = L.order == WO_GROUPED ? (int64_t)kXcds * grouped_tiles((int)ntl) * nchunk
-                                                 : (ntl * nchunk + kXcds - 1) / kXcds * kXcds;
+    const int64_t blocks = eval_blocks(L, yb ? g.nytiles : g.ntiles);
     if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks), block(NT);
     switch (L.kind) {

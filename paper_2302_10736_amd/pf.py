@@ -30,7 +30,8 @@ EXPORTS = (
     "pf_build_pattern", "pf_grid_free", "pf_grid_sizes", "pf_pattern_sizes", "pf_grid_offsets",
     "pf_pattern_export", "pf_ybus", "pf_injections_elementwise", "pf_injections_ybus", "pf_jacobian_values",
     "pf_injections_vjp", "pf_jacobian_two_phase_static", "pf_branch_flows", "pf_phasors", "pf_ybus_from_phasors", "pf_jacobian_map", "pf_jacobian_scatter", "pf_set_schedule", "pf_get_schedule", "pf_graph_create", "pf_graph_launch",
-    "pf_graph_free", "pf_autotune", "pf_stream_copy", "pf_debug_fail_allocs", "pf_last_error", "pf_version",
+    "pf_graph_free", "pf_autotune", "pf_stream_copy", "pf_debug_fail_allocs",
+    "pf_debug_launch", "pf_last_error", "pf_version",
 )
 PF_OP_INJECTIONS, PF_OP_JACOBIAN, PF_OP_VJP = 0, 1, 2
 
@@ -82,6 +83,7 @@ def lib() -> C.CDLL:
         L.pf_jacobian_scatter.argtypes = [P, i32, P, P, i64, P, P]
         L.pf_stream_copy.argtypes = [P, P, i64, P]
         L.pf_debug_fail_allocs.argtypes = [i32]
+        L.pf_debug_launch.argtypes = [P, i32, i32, i32, P]
         L.pf_ybus_from_phasors.argtypes = [P, i32, i32, P, P, P, P, P]
         L.pf_set_schedule.argtypes = [P, i32, i32, i32]
         L.pf_graph_create.argtypes = [P, P, i32, C.POINTER(P)]
@@ -395,6 +397,15 @@ def pf_debug_fail_allocs(n: int):
     """Make the library's next ``n`` device allocations fail as out of memory
     (testing aid, include/pf_testing.h)."""
     check(lib().pf_debug_fail_allocs(int(n)))
+
+
+def pf_debug_launch(grid: "Grid", op: int, method: int, nstate: int):
+    """(states per workgroup, work order, read-ahead, workgroups, threads per
+    workgroup) of the launch for ``op`` (PF_OP_*) and ``method`` under the
+    grid's present schedule (testing aid, include/pf_testing.h)."""
+    out = np.zeros(5, np.int64)
+    check(lib().pf_debug_launch(grid.handle, int(op), int(method), int(nstate), _hp(out)))
+    return tuple(int(v) for v in out)
 
 
 def pf_version() -> str:

@@ -83,3 +83,22 @@ def test_failed_build_reports_enomem():
     p, q, _ = _sj(G, to_dev(vm_h), to_dev(va_h))
     p_o, _ = oracle.inject_ew(g, vm_h[0], va_h[0])
     assert rel_err(p[0], p_o) <= TOL
+
+
+# A bus of 300 branch ends: one or two pieces of a 256-record tile, five of a
+# 64-record one, which takes other launches.
+def test_failed_schedule_change_keeps_the_launches():
+    g = gridgen.make_grid(2_000, 2_600, 0.15, case=9)
+    far = np.setdiff1d(np.arange(2_000), [700])[::6][:300]
+    cat = lambda a, b: np.concatenate([a, np.full(len(far), b)])  # noqa: E731
+    g = gridgen.Grid(g.nb, g.nl + len(far), cat(g.fbus, 700).astype(np.int32), np.concatenate([g.tbus, far]).astype(np.int32),
+                     cat(g.r, 0.01), cat(g.x, 0.1), cat(g.b, 0.02), cat(g.tap, 1.0), cat(g.shift, 0.0), g.gs, g.bs)
+    G = pf.Grid.from_grid(g)
+    calls = [(op, m, ns) for op, m in ((pf.PF_OP_INJECTIONS, pf.PF_METHOD_ELEMENTWISE), (pf.PF_OP_VJP, 0),
+                                       (pf.PF_OP_JACOBIAN, pf.PF_METHOD_ELEMENTWISE)) for ns in (1, 64, 700)]
+    before = [pf.pf_debug_launch(G, *c) for c in calls]
+    pf.pf_debug_fail_allocs(1)
+    with pytest.raises(pf.PFError):
+        G.set_schedule(64, 0, pf.PF_ORDER_AUTO)
+    pf.pf_debug_fail_allocs(0)
+    assert [pf.pf_debug_launch(G, *c) for c in calls] == before
