@@ -995,8 +995,10 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (nstate <= 1) return 1;
     const bool yb = kind == pf::K_YB_S || kind == pf::K_YB_SJ || kind == pf::K_YB_SJ_CSC;
     const int64_t nt = std::max<int64_t>(1, (int64_t)(yb ? g->ytiles : g->tiles).size());
-    // A launch holds less than 2^32 threads: at most 2^22 workgroups.
-    const int least = (int)std::min<int64_t>(nstate, (nt * nstate + (1 << 22) - 1) >> 22);
+    // A launch holds less than 2^32 threads: at most 2^22 workgroups.  The
+    // grouped order has one for every tile of eight equal shares.
+    const int64_t slots = work_order(g, kind, nstate) == pf::WO_GROUPED ? (nt + 7) / 8 * 8 : nt;
+    const int least = (int)std::min<int64_t>(nstate, (slots * nstate + (1 << 22) - 1) >> 22);
     if (g->long_rows && g->order == PF_ORDER_AUTO) return least;
     if (g->scattered && g->order == PF_ORDER_AUTO)
         return std::max(least, is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1);

@@ -1856,7 +1856,7 @@ hipError_t launch_nt(const DevGrid &g, const Launch &L, hipStream_t st) {
     const int nchunk = (int)(((int64_t)L.nstate + spb - 1) / spb);
     const bool yb = L.kind == K_YB_S || L.kind == K_YB_SJ || L.kind == K_YB_SJ_CSC;
     const int64_t blocks = eval_blocks(L, yb ? g.nytiles : g.ntiles);
-    if (blocks > INT32_MAX) return hipErrorInvalidConfiguration;
+    if (blocks * NT >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks), block(NT);
     switch (L.kind) {
         case K_EW_S:
