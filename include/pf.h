@@ -301,8 +301,8 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     automatic: at most 4 for Jacobian launches, 8 for
  *                     injections and 16 for the adjoint (32 if its tiles just
  *                     fill the GPU), fewer when they do not fill it; with PF_ORDER_AUTO on grids
- *                     numbered without regard to the network 1 or 2, and 1
- *                     on grids with rows of more than two tiles)
+ *                     numbered without regard to the network 1 or 2).  Tiles
+ *                     with a row of more than 64 terms take one in any case
  *   order             order of the (tile, state chunk) work items over the
  *                     workgroups: PF_ORDER_TILE_MAJOR (the state chunks of
  *                     one tile are adjacent), PF_ORDER_STATE_MAJOR (the tiles
@@ -317,8 +317,7 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     injections: tile-major, so the state chunks of one
  *                     tile share an L2, or grouped for many states or
  *                     grids; all of them state-major on grids numbered
- *                     without regard to the network or with rows of more
- *                     than two tiles)
+ *                     without regard to the network)
  * The initial schedule is tile_items 256 (with several grids per handle:
  * the smallest of 64, 128, 256 that holds the mean branch ends per grid,
  * since tiles never span grids), states_per_block 0, PF_ORDER_AUTO.

@@ -68,7 +68,7 @@ struct Arena {
 struct Tiling {
     int32_t tile_items = 256;
     std::vector<pf::TileDesc> tiles, ytiles;  // element-wise and Ybus work tiles
-    bool long_rows = false;                   // some row takes three or more pieces of a tile (see work_order)
+    std::vector<int32_t> slow_tiles, slow_ytiles;  // indices of the slow ones
 };
 
 }  // namespace
@@ -127,11 +127,11 @@ void build_tiles(pf_grid *g, int NT) {
             d.r0 = a;
             d.nrows = z - a;
             d.i0 = g->irow[a];
-            d.n = g->irow[z] - d.i0;
-            d.ne = d.n - (z - a);  // one shunt record per row
+            d.ne = g->irow[z] - d.i0 - (z - a);  // one shunt record per row
             d.s0 = g->yrow[a];
             d.ns = g->yrow[z] - d.s0;
             d.sh = 0;
+            d.slow = 0;
             if (z == a + 1)  // one row: where its bus-shunt record sits among its records
                 for (int32_t e = g->irow[a]; e < g->irow[z]; ++e)
                     if (g->item_br[e] < 0) d.sh = e - d.i0;
@@ -176,8 +176,27 @@ void build_tiles(pf_grid *g, int NT) {
         }
         close(g->ytiles, re);
     }
-    g->long_rows = false;
-    for (const pf::TileDesc &c : g->tiles) g->long_rows |= c.ne > 2 * NT;
+    // Tiles with a slow row, longest first.  A row longer than a tile keeps
+    // nothing between states, so its tile is always among them; packed tiles
+    // do, and are only while they are few.
+    auto choose = [NT](std::vector<pf::TileDesc> &all, int32_t pf::TileDesc::*len, const std::vector<int32_t> &row, int32_t extra,
+                       std::vector<int32_t> &out) {
+        std::vector<int32_t> longest(all.size(), 0);
+        int64_t slow = 0;
+        for (size_t t = 0; t < all.size(); ++t) {
+            for (int32_t i = all[t].r0; i < all[t].r0 + all[t].nrows; ++i)
+                longest[t] = std::max(longest[t], row[i + 1] - row[i] - extra);
+            slow += longest[t] > pf::kSlowRow;
+        }
+        out.clear();
+        for (size_t t = 0; t < all.size(); ++t) {
+            all[t].slow = all[t].*len > NT || (longest[t] > pf::kSlowRow && 8 * slow <= (int64_t)all.size());
+            if (all[t].slow) out.push_back((int32_t)t);
+        }
+        std::stable_sort(out.begin(), out.end(), [&](int32_t a, int32_t b) { return longest[a] > longest[b]; });
+    };
+    choose(g->tiles, &pf::TileDesc::ne, g->irow, 1, g->slow_tiles);  // branch ends: all records but the shunt's
+    choose(g->ytiles, &pf::TileDesc::ns, g->yrow, 0, g->slow_ytiles);
 }
 
 // Lane tables of the packed tiles (tile size NT).  Positions inside the LDS
@@ -190,7 +209,7 @@ void build_tiles(pf_grid *g, int NT) {
 struct HostLanes {
     std::vector<int32_t> lane_j, lane_rec, lane_pk, lane_run;
     std::vector<int32_t> ylane_j, ylane_slot, ylane_pk;
-    std::vector<int32_t> row_ew, row_yb;                 // pairs per bus, + one inert entry at nb
+    std::vector<int32_t> row_ew, row_yb;                 // pairs per bus, + one inert entry at nb, + the slow tiles
     std::vector<int32_t> ydslot;                         // [nb] global Ybus slot of each diagonal
     std::vector<int32_t> yt_slot;                        // [nnz_y] slot of the transposed entry
     std::vector<int32_t> ylane_tslot;                    // transposed slot of each Ybus lane, -1 inert
@@ -213,6 +232,8 @@ HostLanes build_lanes(const pf_grid *g) {
     h.row_yb.assign(2 * ((size_t)g->nb + 1), 0);
     h.row_ew[2 * (size_t)g->nb + 1] = epad | (epad << 16);
     h.row_yb[2 * (size_t)g->nb + 1] = ypad;
+    for (int32_t t : g->slow_tiles) h.row_ew.insert(h.row_ew.end(), {t, 0});
+    for (int32_t t : g->slow_ytiles) h.row_yb.insert(h.row_yb.end(), {t, 0});
     h.ydslot.assign(g->nb, 0);
     auto diag_slot = [&](int32_t i) {
         for (int32_t q = g->yrow[i]; q < g->yrow[i + 1]; ++q)
@@ -299,9 +320,9 @@ int upload_tiles(pf_grid *g) {
     const size_t o_t = ar.take<pf::TileDesc>(nt), o_yt = ar.take<pf::TileDesc>(nyt);
     const size_t o_lj = ar.take<int32_t>(nle), o_lrec = ar.take<int32_t>(nle), o_lpk = ar.take<int32_t>(nle);
     const size_t o_lrun = ar.take<int32_t>(nrun);
-    const size_t o_lgb = ar.take<double2>(nle), o_lgr = ar.take<double2>(nle), o_rew = ar.take<int2>(g->nb + 1);
+    const size_t o_lgb = ar.take<double2>(nle), o_lgr = ar.take<double2>(nle), o_rew = ar.take<int2>(h.row_ew.size() / 2);
     const size_t o_yj = ar.take<int32_t>(nly), o_yslot = ar.take<int32_t>(nly), o_ypk = ar.take<int32_t>(nly);
-    const size_t o_yy = ar.take<double2>(nly), o_ryb = ar.take<int2>(g->nb + 1);
+    const size_t o_yy = ar.take<double2>(nly), o_ryb = ar.take<int2>(h.row_yb.size() / 2);
     const size_t o_yds = ar.take<int32_t>(g->nb);
     const size_t o_yts = ar.take<int32_t>(g->nnz_y), o_ylt = ar.take<int32_t>(nly), o_yyt = ar.take<double2>(nly);
     void *mem = nullptr;
@@ -320,11 +341,11 @@ int upload_tiles(pf_grid *g) {
     up(o_lrec, h.lane_rec.data(), nle * 4);
     up(o_lpk, h.lane_pk.data(), nle * 4);
     up(o_lrun, h.lane_run.data(), nrun * 4);
-    up(o_rew, h.row_ew.data(), ((size_t)g->nb + 1) * 8);
+    up(o_rew, h.row_ew.data(), h.row_ew.size() * 4);
     up(o_yj, h.ylane_j.data(), nly * 4);
     up(o_yslot, h.ylane_slot.data(), nly * 4);
     up(o_ypk, h.ylane_pk.data(), nly * 4);
-    up(o_ryb, h.row_yb.data(), ((size_t)g->nb + 1) * 8);
+    up(o_ryb, h.row_yb.data(), h.row_yb.size() * 4);
     up(o_yds, h.ydslot.data(), (size_t)g->nb * 4);
     up(o_yts, h.yt_slot.data(), (size_t)g->nnz_y * 4);
     up(o_ylt, h.ylane_tslot.data(), nly * 4);
@@ -949,11 +970,7 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 // from the states of all resident workgroups at once (100k buses renumbered at
 // random, injections of 100 states: tile-major 924 us, grouped 577,
 // state-major with 8 states per workgroup 586, with one 315; adjoint of 60k x
-// 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).  Long
-// rows take the same order with one state per workgroup: the workgroup of a
-// row walks its pieces one after another, so its states have to go to
-// different workgroups (20k buses with 20 hubs x 64 states: injections 83 us
-// tile-major with 8 states, 43; adjoint 307 and 67; S+J 77 grouped, 63).
+// 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).
 // Injections of many states or grids are grouped too (100k x 128 163 us
 // tile-major, 154 grouped; 43 grids of 728 to 4,838 buses x 70 200 and 162), of
 // fewer not (60k x 40 27.2 and 28.3).
@@ -966,7 +983,7 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
         case PF_ORDER_GROUPED:
             return pf::WO_GROUPED;
         default:
-            if (g->scattered || g->long_rows) return pf::WO_STATE;
+            if (g->scattered) return pf::WO_STATE;
             if (kind == pf::K_EW_S || kind == pf::K_YB_S)
                 return table_bytes(g, kind) >= (int64_t)1 << 19 && (nstate >= 64 || g->ngrids > 1) ? pf::WO_GROUPED : pf::WO_TILE;
             if (table_bytes(g, kind) >= (int64_t)1 << 19) return pf::WO_GROUPED;
@@ -999,7 +1016,6 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     // grouped order has one for every tile of eight equal shares.
     const int64_t slots = work_order(g, kind, nstate) == pf::WO_GROUPED ? (nt + 7) / 8 * 8 : nt;
     const int least = (int)std::min<int64_t>(nstate, (slots * nstate + (1 << 22) - 1) >> 22);
-    if (g->long_rows && g->order == PF_ORDER_AUTO) return least;
     if (g->scattered && g->order == PF_ORDER_AUTO)
         return std::max(least, is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1);
     int per_cu = pf::resident_blocks_per_cu(kind, g->tile_items, g->has_parallel);
@@ -1043,8 +1059,9 @@ int ahead_of(const pf_grid *g, const pf::Launch &L) {
     // Inputs that fit in half of the 256 MB memory-side cache may be there, and
     // then reading ahead only costs (100k x 32, 51 MB: 80 us without, 88 with).
     if ((int64_t)L.nstate * g->nb * 16 < (int64_t)128 << 20) return 0;
-    const int64_t burst = 8, dist = 256 / walk + 1;
-    if (L.nstate < dist + burst || walk < 8) return 0;  // fewer states: nothing to gain (40k buses x 8: 1 % lost)
+    if (walk < 8) return 0;
+    const int64_t burst = 8, dist = 256 / walk + 1;  // dist: at most 33
+    if (L.nstate < dist + burst) return 0;  // fewer states: nothing to gain (40k buses x 8: 1 % lost)
     if ((burst + dist) * 2 * (int64_t)g->nb > (int64_t)3 << 20) return 0;  // 16 bytes a bus, an eighth of the buses
     return (int)(burst | dist << 8);
 }
@@ -1071,7 +1088,12 @@ void plan(const pf_grid *g, pf::Launch &L) {
     L.has_parallel = g->has_parallel;
     L.states_per_block = auto_states_per_block(g, L.kind, L.nstate);
     L.order = work_order(g, L.kind, L.nstate);
-    L.ahead = ahead_of(g, L);
+    // Several states: tiles with slow rows get work items of their own, at most
+    // 2^21 of them beside the 2^22 others.
+    const bool yb = L.kind == pf::K_YB_S || L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
+    const int64_t own = (int64_t)(yb ? g->slow_ytiles : g->slow_tiles).size();
+    L.own = L.nstate > 1 && own * L.nstate <= (int64_t)1 << 21 ? (int)own : 0;
+    L.ahead = L.own ? 0 : ahead_of(g, L);
 }
 
 int run(const pf_grid *g, pf::Launch &L, void *stream) {

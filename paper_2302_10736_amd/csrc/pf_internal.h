@@ -11,11 +11,17 @@
 
 namespace pf {
 
+// Rows of more terms than this make their tile slow: a row longer than the tile
+// is walked in pieces, and a packed row is added up by one thread four terms at
+// a time (250 in about 7 us, where a state of a tile takes 1 to 2 us).  The
+// states of slow tiles go to different workgroups (next_item in pf_kernels.hip).
+constexpr int kSlowRow = 64;
+
 // One work tile: consecutive whole bus rows of one grid (see pf_kernels.hip).
 struct TileDesc {
     int32_t r0, nrows;  // first row (global bus), number of rows
-    int32_t i0, n;      // first record, number of records (shunt records included)
-    int32_t ne;         // branch-end records (n - nrows)
+    int32_t i0, slow;   // first record; 1 for a slow tile (else 0)
+    int32_t ne;         // branch-end records (the rows' shunt records come on top)
     int32_t s0, ns;     // first Ybus slot, number of slots
     int32_t sh;         // one-row tiles: position of the bus-shunt record in the row (else 0)
     int64_t jp, jq;     // offsets of the tile's P rows and Q rows in one state's J values
@@ -72,11 +78,11 @@ struct DevGrid {
     const int32_t *lane_run;    // with parallel branches: records of the slot (first record of a slot), else 0
     const double2 *lane_gb;     // {G, B}
     const double2 *lane_grbr;   // {Gr, Br}
-    const int2 *row_ew;         // [nb+1] {ra | rz << 16, d11 | d12 << 16}; [nb] inert
+    const int2 *row_ew;         // [nb+1] {ra | rz << 16, d11 | d12 << 16}; [nb] inert; then {tile, 0} of the slow tiles
     const int32_t *ylane_j;     // Ybus nonzero: column bus
     const int32_t *ylane_pk;    // yb_pack(o11, o12, row, diag)
     const double2 *ylane_y;     // {Re Y, Im Y}
-    const int2 *row_yb;         // [nb+1] {ya | yz << 16, dls}; [nb] inert
+    const int2 *row_yb;         // [nb+1] {ya | yz << 16, dls}; [nb] inert; then {tile, 0} of the slow tiles
     const double2 *ylane_yt;    // Ybus lane: {Re, Im} of the transposed entry Y_ji (CSC Jacobian)
     const int32_t *yt_slot;     // [nnz_y] slot of the transposed entry (long rows, CSC Jacobian)
 };
@@ -145,6 +151,7 @@ struct Launch {
     int states_per_block;
     int order;             // WO_*
     int ahead;             // states read ahead (read_ahead in pf_kernels.hip): burst | dist << 8, 0 none
+    int own;               // slow tiles, which get a work item per state (next_item), 0 with one state
     int nstate;
     bool has_parallel;
     const double *vm, *va, *lp, *lq;
@@ -158,8 +165,9 @@ constexpr int kXcds = 8;
 // Workgroups of a launch over ntiles tiles (see work_item in pf_kernels.hip).
 inline int64_t eval_blocks(const Launch &L, int64_t ntiles) {
     const int64_t nchunk = ((int64_t)L.nstate + L.states_per_block - 1) / L.states_per_block;
-    return L.order == WO_GROUPED ? kXcds * ((ntiles + kXcds - 1) / kXcds) * nchunk
-                                 : (ntiles * nchunk + kXcds - 1) / kXcds * kXcds;
+    const int64_t front = ((int64_t)L.own * L.nstate + kXcds - 1) / kXcds * kXcds;
+    return front + (L.order == WO_GROUPED ? kXcds * ((ntiles + kXcds - 1) / kXcds) * nchunk
+                                          : (ntiles * nchunk + kXcds - 1) / kXcds * kXcds);
 }
 
 hipError_t launch_eval(const DevGrid &g, const Launch &L, hipStream_t stream);

@@ -89,11 +89,11 @@ __device__ __forceinline__ void sincos_dev(double x, double *s, double *c) {
 // Workgroups are dispatched round-robin over the 8 XCDs.  Give each XCD a
 // contiguous range of work items so that neighbouring tiles, and all state
 // chunks of one tile, share one L2.
-__device__ __forceinline__ int work_index(int nblocks) {
-    const int b = blockIdx.x;
+__device__ __forceinline__ int work_index(int b, int nblocks) {
     const int per = nblocks / kXcds;
     return (b % kXcds) * per + b / kXcds;
 }
+__device__ __forceinline__ int work_index(int nblocks) { return work_index(blockIdx.x, nblocks); }
 
 // Tiles per XCD in the grouped order.
 __host__ __device__ __forceinline__ int grouped_tiles(int ntiles) { return (ntiles + kXcds - 1) / kXcds; }
@@ -110,22 +110,22 @@ __host__ __device__ __forceinline__ int grouped_tiles(int ntiles) { return (ntil
 //               XCD's L2 across chunks while consecutive workgroups write
 //               neighbouring rows of one state's outputs.  The grid has
 //               8 tx nchunk workgroups.
-__device__ __forceinline__ bool work_item(int ntiles, int nchunk, int order, int &t, int &c) {
+__device__ __forceinline__ bool work_item(int b, int nblocks, int ntiles, int nchunk, int order, int &t, int &c) {
     if (nchunk == 1) {  // one chunk: every order maps tile = work_index (and the grids agree)
-        t = work_index(gridDim.x);
+        t = work_index(b, nblocks);
         c = 0;
         return t < ntiles;
     }
     if (order == WO_GROUPED) {
         const int tx = grouped_tiles(ntiles);
-        const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
+        const int x = b % kXcds, i = b / kXcds;
         const int ntx = min(tx, ntiles - x * tx);  // tiles of XCD x (<= 0: none)
         if (ntx <= 0 || i >= ntx * nchunk) return false;
         t = x * tx + i % ntx;
         c = i / ntx;
         return true;
     }
-    const int w = work_index(gridDim.x);
+    const int w = work_index(b, nblocks);
     if (w >= ntiles * nchunk) return false;
     if (order == WO_STATE) {
         t = w % ntiles;
@@ -134,6 +134,49 @@ __device__ __forceinline__ bool work_item(int ntiles, int nchunk, int order, int
         t = w / nchunk;
         c = w - t * nchunk;
     }
+    return true;
+}
+
+// Slow tiles (TileDesc::slow): with OWN their states are work items of their own,
+// one per (tile, state), in front of the others and spread over the XCDs by
+// state: one thread adds up a row, or the workgroup walks its pieces one after
+// another, so with several states, or with all states of a row on one XCD, they
+// would outlast the launch.  `order` holds the number of these tiles above its
+// low four bits, and `own` (entries g.nb + 1 ... of the row table) lists them.
+// Their ordinary items have nothing left to do.  An XCD's own items are of
+// neighbouring states, whose arrays its L2 holds for the gathers.  20k buses with
+// 20 rows of 200 to 2,000 branch ends x 64 states: injections 35.5 us (one state
+// per workgroup for all tiles 42.2, walked among the other states 76.6), adjoint
+// 61 (67.7, 311), S+J 57 (64.6, 82); 100k buses with one row of 513 x 128:
+// injections 127 us (214, 129), adjoint 243 (341, 995), S+J 320 (438, 323).  The
+// other instantiations stay free of this: with it they took 1 to 3 % longer.
+struct Item {
+    int t, sb, se;  // tile, states [sb, se)
+    bool own;       // an own item: one state of a slow tile
+};
+
+template <bool OWN>
+__device__ __forceinline__ bool next_item(int ntiles, int nstate, int spb, int nchunk, int order, const int2 *own, Item &m) {
+    int c;
+    if constexpr (OWN) {
+        const int n = order >> 4, items = n * nstate, front = (items + kXcds - 1) / kXcds * kXcds;
+        const int b = blockIdx.x;
+        m.own = b < front;
+        if (m.own) {
+            const int i = work_index(b, front);
+            if (i >= items) return false;
+            m.t = own[i % n].x;
+            m.sb = i / n;
+            m.se = m.sb + 1;
+            return true;
+        }
+        if (!work_item(b - front, gridDim.x - front, ntiles, nchunk, order & 15, m.t, c)) return false;
+    } else {
+        m.own = false;
+        if (!work_item(blockIdx.x, gridDim.x, ntiles, nchunk, order, m.t, c)) return false;
+    }
+    m.sb = c * spb;
+    m.se = min(nstate, m.sb + spb);
     return true;
 }
 
@@ -146,6 +189,9 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 using Tile = TileDesc;
+
+// Extras of an instantiation.
+enum { EX_NONE = 0, EX_AHEAD = 1, EX_OWN = 2 };
 
 __device__ __forceinline__ Tile tile_of(const DevGrid &g, int t) { return g.tiles[t]; }
 
@@ -265,10 +311,11 @@ __device__ __forceinline__ int ew_row(int v) { return (int)((unsigned)v >> 22); 
 // the compiler wait for every outstanding operation where the paths join,
 // prefetch included.  So every pair runs both of its states; when the count
 // is odd, the last pair evaluates the last state twice and writes the same
-// values to the same places again.  `proc(s, parity, in)` gets the parity of
-// the state's position for the double-buffered LDS.
-template <class In, bool ONE, class Load, class Proc>
-__device__ __forceinline__ void pipelined_states(int sb, int se, In &ra, Load &&load, Proc &&proc) {
+// values to the same places again; only an own item (Item::own, one state, two
+// barriers of serial sums long) leaves after the first.  `proc(s, parity, in)`
+// gets the parity of the state's position for the double-buffered LDS.
+template <class In, bool ONE, bool OWN, class Load, class Proc>
+__device__ __forceinline__ void pipelined_states(int sb, int se, bool own, In &ra, Load &&load, Proc &&proc) {
     if constexpr (ONE) {  // one state per workgroup: nothing to overlap, half the registers
         proc(sb, 0, ra);
         return;
@@ -278,6 +325,7 @@ __device__ __forceinline__ void pipelined_states(int sb, int se, In &ra, Load &&
         const int s1 = min(s + 1, se - 1);
         load(s1, rb);
         proc(s, 0, ra);
+        if (OWN && own) break;
         load(min(s + 2, se - 1), ra);
         proc(s1, 1, rb);
     }
@@ -290,10 +338,10 @@ __device__ __forceinline__ void pipelined_states(int sb, int se, In &ra, Load &&
 // where four (three with parallel branches) prefetched their own: 300k buses x
 // 16 states 161 -> 153 us, 300k x 3 with parallel circuits 43.1 -> 33.1 us, 64
 // grids of 1k to 80k buses x 4 states 181 -> 170 us.
-template <class In, bool ONE, bool WITH_J, class Load, class Proc>
-__device__ __forceinline__ void states_loop(int sb, int se, In &ra, Load &&load, Proc &&proc) {
+template <class In, bool ONE, bool WITH_J, bool OWN, class Load, class Proc>
+__device__ __forceinline__ void states_loop(int sb, int se, bool own, In &ra, Load &&load, Proc &&proc) {
     if constexpr (ONE || !WITH_J) {
-        pipelined_states<In, ONE>(sb, se, ra, load, proc);
+        pipelined_states<In, ONE, OWN>(sb, se, own, ra, load, proc);
     } else {
         for (int s = sb;;) {
             proc(s, 0, ra);
@@ -459,12 +507,14 @@ __device__ __forceinline__ EwRow ew_row(double vi, double dA, double dC, double 
 // column-major order (WITH_J only) with the same tiles and staging, each
 // record's slot filled by ew_record_csc and the diagonal entries
 // dQ_i/dtheta_i and dP_i/dv_i trading places.
-// AHEAD (one state per workgroup, WITH_J): see read_ahead.
-template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC, bool AHEAD>
+// EX: EX_AHEAD (one state per workgroup, WITH_J) see read_ahead, EX_OWN see work_item.
+template <int NT, bool PAR, bool WITH_J, bool ONE, bool CSC, int EX>
 __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
     static_assert(WITH_J || !CSC, "the CSC order concerns J values");
+    constexpr bool AHEAD = EX == EX_AHEAD, OWN = EX == EX_OWN;
+    static_assert(!AHEAD || (WITH_J && ONE), "read-ahead is for one state per workgroup, with J");
     constexpr int NR = (WITH_J && PAR) ? NT : 1;  // remote partials kept for slot sums
     constexpr int NBUF = ONE || WITH_J ? 1 : 2;   // injections alternate between two LDS buffers
     constexpr int NS = kEwSlots(NT);              // Ybus slots per tile
@@ -475,10 +525,9 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
     __shared__ __align__(16) double s_J[NBUF][WITH_J ? kJStage<NS> : 2];
     __shared__ double s_rem[NBUF][4][NR];
 
-    int t, c0;
-    if (!work_item(g.ntiles, nchunk, AHEAD ? (int)WO_GROUPED : order, t, c0)) return;
-    const int sb = c0 * spb;
-    const int se = min(nstate, sb + spb);
+    Item item;
+    if (!next_item<OWN>(g.ntiles, nstate, spb, nchunk, AHEAD ? (int)WO_GROUPED : order, g.row_ew + g.nb + 1, item)) return;
+    const int t = item.t, sb = item.sb, se = item.se;
     const int k = threadIdx.x;
     // lane table entries do not depend on the tile descriptor: both load at once
     const size_t lane = (size_t)t * NT + k;
@@ -490,6 +539,8 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
     const Tile c = tile_of(g, t);
     const size_t nb = (size_t)g.nb;
 
+    if constexpr (OWN)
+        if (c.slow && !item.own) return;  // its states have items of their own
     if (c.ne > NT) {
         // ---- one row with more than NT branch ends, walked in pieces of NT
         // branch ends (position p of the row's branch ends is record
@@ -767,26 +818,26 @@ __device__ __forceinline__ void ew_eval(const DevGrid &g, int nstate, int spb, i
             write_jrows<NT, NS>(c, s_J[p], J + (size_t)s * (size_t)g.nnz_j);
         }
     };
-    states_loop<In, ONE, WITH_J>(sb, se, first, load, proc);
+    states_loop<In, ONE, WITH_J, OWN>(sb, se, item.own, first, load, proc);
     if constexpr (AHEAD) ahead_done(later);
 }
 
 // The injections of several states per workgroup are held to 80 registers
 // (their natural count is a few above), so that six waves fit per SIMD
 // instead of five.
-template <int NT, bool PAR, bool WITH_J, bool ONE, bool AHEAD>
+template <int NT, bool PAR, bool WITH_J, bool ONE, int EX>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((!ONE && !WITH_J) ? 6 : 1, 8)))
     k_ew(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
          double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, WITH_J, ONE, false, AHEAD>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
+    ew_eval<NT, PAR, WITH_J, ONE, false, EX>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
 }
 
 // Injections and J values in CSC order.
-template <int NT, bool PAR, bool ONE, bool AHEAD>
+template <int NT, bool PAR, bool ONE, int EX>
 __global__ void __launch_bounds__(NT)
     k_ew_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
              const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    ew_eval<NT, PAR, true, ONE, true, AHEAD>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
+    ew_eval<NT, PAR, true, ONE, true, EX>(g, nstate, spb, nchunk, order, vm, va, P, Q, J);
 }
 
 // ===================================================================
@@ -889,22 +940,23 @@ __device__ __forceinline__ void yb_phasor(const YbIn &x, Cx &V, Cx &U) {
 // evaluation of row j rounds them (CSC values = CSR values transposed, bit
 // for bit), and the diagonal entries dQ_i/dtheta_i and dP_i/dv_i trade
 // places.
-template <int NT, bool WITH_J, bool ONE, int PH, bool CSC, bool AHEAD>
+template <int NT, bool WITH_J, bool ONE, int PH, bool CSC, int EX>
 __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, int nchunk, int order,
                                         const double *__restrict__ vm, const double *__restrict__ va,
                                         const double *__restrict__ ph, double *__restrict__ P,
                                         double *__restrict__ Q, double *__restrict__ J) {
     static_assert(!CSC || (WITH_J && PH == PH_FLY), "the CSC order concerns J values");
+    constexpr bool AHEAD = EX == EX_AHEAD, OWN = EX == EX_OWN;
+    static_assert(!AHEAD || (WITH_J && ONE && PH == PH_FLY), "read-ahead is for one state per workgroup, with J");
     constexpr int NBUF = ONE || WITH_J ? 1 : 2;
     __shared__ double s_yv[NBUF][2][NT];  // Y_ij V_j
     __shared__ double s_vu[NBUF][4][NT];  // per row: V_i, U_i (re, im)
     __shared__ double s_yd[WITH_J ? 2 : 1][WITH_J ? NT : 1];  // per row: Y_ii (state-free, written once)
     __shared__ __align__(16) double s_J[NBUF][WITH_J ? kJStage<NT> : 2];
 
-    int t, c0;
-    if (!work_item(g.nytiles, nchunk, AHEAD ? (int)WO_GROUPED : order, t, c0)) return;
-    const int sb = c0 * spb;
-    const int se = min(nstate, sb + spb);
+    Item item;
+    if (!next_item<OWN>(g.nytiles, nstate, spb, nchunk, AHEAD ? (int)WO_GROUPED : order, g.row_yb + g.nb + 1, item)) return;
+    const int t = item.t, sb = item.sb, se = item.se;
     const int k = threadIdx.x;
     const size_t lane = (size_t)t * NT + k;
     const int j = g.ylane_j[lane];
@@ -915,6 +967,8 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
     const Tile c = g.ytiles[t];
     const size_t nb = (size_t)g.nb;
 
+    if constexpr (OWN)
+        if (c.slow && !item.own) return;  // its states have items of their own
     if (c.ns > NT) {
         // ---- one long row: pass 1 sums I_i in pieces of NT nonzeros (chunk sums in parallel,
         // folded in row_sum2's order by one thread, each piece's fold overlapping the next piece's
@@ -1100,23 +1154,23 @@ __device__ __forceinline__ void yb_eval(const DevGrid &g, int nstate, int spb, i
             write_jrows<NT, NT>(c, s_J[p], J + (size_t)s * (size_t)g.nnz_j);
         }
     };
-    states_loop<In, ONE, WITH_J>(sb, se, first, load, proc);
+    states_loop<In, ONE, WITH_J, OWN>(sb, se, item.own, first, load, proc);
     if constexpr (AHEAD) ahead_done(later);
 }
 
-template <int NT, bool WITH_J, bool ONE, int PH, bool AHEAD>
+template <int NT, bool WITH_J, bool ONE, int PH, int EX>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ONE ? 6 : 1, 8)))
     k_ybus(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm, const double *__restrict__ va,
            const double *__restrict__ ph, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    yb_eval<NT, WITH_J, ONE, PH, false, AHEAD>(g, nstate, spb, nchunk, order, vm, va, ph, P, Q, J);
+    yb_eval<NT, WITH_J, ONE, PH, false, EX>(g, nstate, spb, nchunk, order, vm, va, ph, P, Q, J);
 }
 
 // Injections and J values in CSC order by the Ybus method.
-template <int NT, bool ONE, bool AHEAD>
+template <int NT, bool ONE, int EX>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ONE ? 6 : 1, 8)))
     k_ybus_csc(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
                const double *__restrict__ va, double *__restrict__ P, double *__restrict__ Q, double *__restrict__ J) {
-    yb_eval<NT, true, ONE, PH_FLY, true, AHEAD>(g, nstate, spb, nchunk, order, vm, va, nullptr, P, Q, J);
+    yb_eval<NT, true, ONE, PH_FLY, true, EX>(g, nstate, spb, nchunk, order, vm, va, nullptr, P, Q, J);
 }
 
 // ===================================================================
@@ -1151,17 +1205,16 @@ __device__ __forceinline__ double vjp_own(double sum, double vi, double lpi, dou
     return fma(2.0 * vi, fma(lpi, dA, -(lqi * dC)), sum);
 }
 
-template <int NT, bool ONE>
+template <int NT, bool ONE, bool OWN>
 __global__ void __launch_bounds__(NT)
     k_ew_vjp(DevGrid g, int nstate, int spb, int nchunk, int order, const double *__restrict__ vm,
              const double *__restrict__ va, const double *__restrict__ lp, const double *__restrict__ lq,
              double *__restrict__ gvm, double *__restrict__ gva) {
     __shared__ double s_val[ONE ? 1 : 2][2][NT];
 
-    int t, c0;
-    if (!work_item(g.ntiles, nchunk, order, t, c0)) return;
-    const int sb = c0 * spb;
-    const int se = min(nstate, sb + spb);
+    Item item;
+    if (!next_item<OWN>(g.ntiles, nstate, spb, nchunk, order, g.row_ew + g.nb + 1, item)) return;
+    const int t = item.t, sb = item.sb, se = item.se;
     const int k = threadIdx.x;
     const size_t lane = (size_t)t * NT + k;
     const int j = g.lane_j[lane];
@@ -1183,6 +1236,8 @@ __global__ void __launch_bounds__(NT)
         return x;
     };
 
+    if constexpr (OWN)
+        if (c.slow && !item.own) return;  // its states have items of their own
     if (c.ne > NT) {
         // one row with more than NT branch ends, in pieces of NT branch ends
         // (the bus-shunt record, position c.sh, contributes nothing and is
@@ -1331,6 +1386,7 @@ __global__ void __launch_bounds__(NT)
             put_own(1, rb);
             lds_barrier();
             finish(s, 0, first);
+            if (OWN && item.own) break;
             load(min(s + 2, se - 1), first);
             record(1, rb);
             put_own(0, first);
@@ -1784,70 +1840,72 @@ __global__ void k_lane_fill(DevLaneFill f, bool ew) {
     }
 }
 
-// Launches with read-ahead (L.ahead, one state per workgroup) run the AHEAD
-// instantiations: the others stay free of its registers.
-template <int NT, bool ONE, bool WITH_J>
+// The kernels' `order`: four bits of work order, and above them what the
+// instantiation takes: read-ahead or the number of tiles with work items of
+// their own (never both).
+int order_word(const Launch &L) { return L.order | (L.ahead | L.own) << 4; }
+
+// Launches with read-ahead (L.ahead, one state per workgroup) or own items of
+// slow tiles (L.own) run instantiations for these: the others stay free of them.
+template <int NT, bool ONE, bool WITH_J, int EX>
 void launch_ybus_ph(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
-    const int order = L.order | L.ahead << 4;
+    constexpr int EXP = EX == EX_AHEAD ? EX_NONE : EX;  // stored phasors: no read-ahead
+    const int order = order_word(L);
     double *J = WITH_J ? L.jval : nullptr;
     switch (L.phasor) {
         case PH_SPLIT:
-            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_SPLIT, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                               L.order, L.vm, L.va, L.ph, L.p, L.q, J);
+            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_SPLIT, EXP>), grid, block, 0, st, g, L.nstate, spb, nchunk,
+                               order, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
         case PH_INTERLEAVED:
-            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_INTERLEAVED, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                               L.order, L.vm, L.va, L.ph, L.p, L.q, J);
+            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_INTERLEAVED, EXP>), grid, block, 0, st, g, L.nstate, spb, nchunk,
+                               order, L.vm, L.va, L.ph, L.p, L.q, J);
             break;
         default:
-            if (ONE && WITH_J && L.ahead)
-                hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, ONE && WITH_J>), grid, block, 0, st, g, L.nstate, spb,
-                                   nchunk, order, L.vm, L.va, L.ph, L.p, L.q, J);
-            else
-                hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, false>), grid, block, 0, st, g, L.nstate, spb, nchunk,
-                                   L.order, L.vm, L.va, L.ph, L.p, L.q, J);
+            hipLaunchKernelGGL((k_ybus<NT, WITH_J, ONE, PH_FLY, EX>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
+                               L.vm, L.va, L.ph, L.p, L.q, J);
             break;
     }
 }
 
-template <int NT, bool ONE>
-hipError_t launch_ybus(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
-    if (L.phasor != PH_FLY && L.phasor != PH_SPLIT && L.phasor != PH_INTERLEAVED) return hipErrorInvalidValue;
-    if (L.kind == K_YB_SJ_CSC) {
-        if (L.phasor != PH_FLY) return hipErrorInvalidValue;
-        const int order = L.order | L.ahead << 4;
-        if (ONE && L.ahead)
-            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
-                               L.vm, L.va, L.p, L.q, L.jval);
-        else
-            hipLaunchKernelGGL((k_ybus_csc<NT, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
-                               L.va, L.p, L.q, L.jval);
-    } else if (L.kind == K_YB_SJ)
-        launch_ybus_ph<NT, ONE, true>(g, L, grid, block, spb, nchunk, st);
-    else
-        launch_ybus_ph<NT, ONE, false>(g, L, grid, block, spb, nchunk, st);
+template <int NT, bool ONE, int EX>
+hipError_t launch_ex(const DevGrid &g, const Launch &L, dim3 grid, int spb, int nchunk, hipStream_t st) {
+    constexpr int EXS = EX == EX_AHEAD ? EX_NONE : EX;  // without J: no read-ahead
+    const dim3 block(NT);
+    const int order = order_word(L);
+    const bool par = L.has_parallel;
+    auto inj = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g, L.nstate, spb, nchunk, order, L.vm, L.va, L.p, L.q, nullptr); };
+    auto jac = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, g, L.nstate, spb, nchunk, order, L.vm, L.va, L.p, L.q, L.jval); };
+    switch (L.kind) {
+        case K_EW_S:
+            par ? inj(k_ew<NT, true, false, ONE, EXS>) : inj(k_ew<NT, false, false, ONE, EXS>);
+            break;
+        case K_EW_SJ:
+            par ? jac(k_ew<NT, true, true, ONE, EX>) : jac(k_ew<NT, false, true, ONE, EX>);
+            break;
+        case K_EW_SJ_CSC:
+            par ? jac(k_ew_csc<NT, true, ONE, EX>) : jac(k_ew_csc<NT, false, ONE, EX>);
+            break;
+        case K_YB_S:
+        case K_YB_SJ:
+        case K_YB_SJ_CSC:
+            if (L.phasor != PH_FLY && L.phasor != PH_SPLIT && L.phasor != PH_INTERLEAVED) return hipErrorInvalidValue;
+            if (L.kind == K_YB_SJ_CSC) {
+                if (L.phasor != PH_FLY) return hipErrorInvalidValue;
+                jac(k_ybus_csc<NT, ONE, EX>);
+            } else if (L.kind == K_YB_SJ)
+                launch_ybus_ph<NT, ONE, true, EX>(g, L, grid, block, spb, nchunk, st);
+            else
+                launch_ybus_ph<NT, ONE, false, EXS>(g, L, grid, block, spb, nchunk, st);
+            break;
+        case K_EW_VJP:
+            hipLaunchKernelGGL((k_ew_vjp<NT, ONE, EX == EX_OWN>), grid, block, 0, st, g, L.nstate, spb, nchunk, order, L.vm,
+                               L.va, L.lp, L.lq, L.gvm, L.gva);
+            break;
+        default:
+            return hipErrorInvalidValue;
+    }
     return hipGetLastError();
-}
-
-template <int NT, bool ONE, bool PAR>
-void launch_ew(const DevGrid &g, const Launch &L, dim3 grid, dim3 block, int spb, int nchunk, hipStream_t st) {
-    const bool ahead = ONE && L.ahead != 0;
-    const int order = L.order | L.ahead << 4;
-    if (L.kind == K_EW_S)
-        hipLaunchKernelGGL((k_ew<NT, PAR, false, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
-                           L.va, L.p, L.q, nullptr);
-    else if (L.kind == K_EW_SJ && ahead)
-        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
-                           L.vm, L.va, L.p, L.q, L.jval);
-    else if (L.kind == K_EW_SJ)
-        hipLaunchKernelGGL((k_ew<NT, PAR, true, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
-                           L.va, L.p, L.q, L.jval);
-    else if (ahead)
-        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, order,
-                           L.vm, L.va, L.p, L.q, L.jval);
-    else
-        hipLaunchKernelGGL((k_ew_csc<NT, PAR, ONE, false>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm,
-                           L.va, L.p, L.q, L.jval);
 }
 
 template <int NT, bool ONE>
@@ -1857,28 +1915,11 @@ hipError_t launch_nt(const DevGrid &g, const Launch &L, hipStream_t st) {
     const bool yb = L.kind == K_YB_S || L.kind == K_YB_SJ || L.kind == K_YB_SJ_CSC;
     const int64_t blocks = eval_blocks(L, yb ? g.nytiles : g.ntiles);
     if (blocks * NT >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)blocks), block(NT);
-    switch (L.kind) {
-        case K_EW_S:
-        case K_EW_SJ:
-        case K_EW_SJ_CSC:
-            if (L.has_parallel)
-                launch_ew<NT, ONE, true>(g, L, grid, block, spb, nchunk, st);
-            else
-                launch_ew<NT, ONE, false>(g, L, grid, block, spb, nchunk, st);
-            break;
-        case K_YB_S:
-        case K_YB_SJ:
-        case K_YB_SJ_CSC:
-            return launch_ybus<NT, ONE>(g, L, grid, block, spb, nchunk, st);
-        case K_EW_VJP:
-            hipLaunchKernelGGL((k_ew_vjp<NT, ONE>), grid, block, 0, st, g, L.nstate, spb, nchunk, L.order, L.vm, L.va, L.lp,
-                               L.lq, L.gvm, L.gva);
-            break;
-        default:
-            return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const dim3 grid((unsigned)blocks);
+    if (L.own) return launch_ex<NT, ONE, EX_OWN>(g, L, grid, spb, nchunk, st);
+    if constexpr (ONE)
+        if (L.ahead) return launch_ex<NT, ONE, EX_AHEAD>(g, L, grid, spb, nchunk, st);
+    return launch_ex<NT, ONE, EX_NONE>(g, L, grid, spb, nchunk, st);
 }
 
 template <int NT, bool ONE>
@@ -1888,28 +1929,28 @@ int occupancy_nt(int kind, bool par) {
     auto q = [&](const void *f) { e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, NT, 0); };
     switch (kind) {
         case K_EW_S:
-            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, false, ONE, false>)
-                  : reinterpret_cast<const void *>(&k_ew<NT, false, false, ONE, false>));
+            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, false, ONE, EX_NONE>)
+                  : reinterpret_cast<const void *>(&k_ew<NT, false, false, ONE, EX_NONE>));
             break;
         case K_EW_SJ:
-            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, true, ONE, false>)
-                  : reinterpret_cast<const void *>(&k_ew<NT, false, true, ONE, false>));
+            q(par ? reinterpret_cast<const void *>(&k_ew<NT, true, true, ONE, EX_NONE>)
+                  : reinterpret_cast<const void *>(&k_ew<NT, false, true, ONE, EX_NONE>));
             break;
         case K_EW_SJ_CSC:
-            q(par ? reinterpret_cast<const void *>(&k_ew_csc<NT, true, ONE, false>)
-                  : reinterpret_cast<const void *>(&k_ew_csc<NT, false, ONE, false>));
+            q(par ? reinterpret_cast<const void *>(&k_ew_csc<NT, true, ONE, EX_NONE>)
+                  : reinterpret_cast<const void *>(&k_ew_csc<NT, false, ONE, EX_NONE>));
             break;
         case K_YB_S:
-            q(reinterpret_cast<const void *>(&k_ybus<NT, false, ONE, PH_FLY, false>));
+            q(reinterpret_cast<const void *>(&k_ybus<NT, false, ONE, PH_FLY, EX_NONE>));
             break;
         case K_YB_SJ:
-            q(reinterpret_cast<const void *>(&k_ybus<NT, true, ONE, PH_FLY, false>));
+            q(reinterpret_cast<const void *>(&k_ybus<NT, true, ONE, PH_FLY, EX_NONE>));
             break;
         case K_YB_SJ_CSC:
-            q(reinterpret_cast<const void *>(&k_ybus_csc<NT, ONE, false>));
+            q(reinterpret_cast<const void *>(&k_ybus_csc<NT, ONE, EX_NONE>));
             break;
         case K_EW_VJP:
-            q(reinterpret_cast<const void *>(&k_ew_vjp<NT, ONE>));
+            q(reinterpret_cast<const void *>(&k_ew_vjp<NT, ONE, false>));
             break;
         default:
             break;

@@ -152,6 +152,43 @@ def test_random_numbering_same_bits(nb, nstate):
         assert all(torch.equal(a, b) for a, b in zip(out, want))
 
 
+# Rows longer than a tile among others, and (10 buses, tile 64) nearly alone, and
+# packed rows of more than 64 terms: their states are work items of their own.
+@pytest.mark.parametrize("tile,nb,nhub,deg,parallel,nstate", [(64, 400, 3, (65, 140), 0, 5), (64, 400, 9, (70, 399), 60, 7),
+                                                              (128, 900, 1, (129, 129), 0, 2), (256, 2_000, 11, (257, 1_300), 300, 9),
+                                                              (512, 2_500, 2, (513, 2_400), 0, 19), (64, 10, 0, (0, 0), 900, 6),
+                                                              (128, 6_000, 2, (66, 120), 40, 5), (256, 9_000, 3, (100, 250), 0, 18)])
+def test_long_rows_several_states_same_bits(tile, nb, nhub, deg, parallel, nstate):
+    import torch
+    from tests import _grids
+    _gpu.require_gpu()
+    G = pf.Grid.from_grid(_grids.random_hubs(nb, nhub, *deg, parallel, seed=nb + nhub))
+    pf.pf_ybus(G)
+    vm, va = (_gpu.to_dev(x) for x in gridgen.states(nb, nstate, case=9, grid=nb))
+    lp, lq = (_gpu.to_dev(x) for x in gridgen.adjoint_seeds(nb, nstate, case=9, grid=nb))
+    ph = [torch.empty(4 * nstate * nb, dtype=torch.float64, device="cuda:0") for _ in range(2)]
+    for layout, buf in zip((pf.PF_PHASOR_SPLIT, pf.PF_PHASOR_INTERLEAVED), ph):
+        pf.pf_phasors(G, layout, vm, va, buf)
+    want = None
+    for spb, order in ((1, pf.PF_ORDER_TILE_MAJOR), (0, pf.PF_ORDER_AUTO), (2, pf.PF_ORDER_TILE_MAJOR), (3, pf.PF_ORDER_STATE_MAJOR),
+                       (4, pf.PF_ORDER_GROUPED), (nstate, pf.PF_ORDER_GROUPED), (nstate + 5, pf.PF_ORDER_AUTO)):
+        G.set_schedule(tile, spb, order)
+        new = lambda n: torch.full((nstate, n), -7.0, dtype=torch.float64, device="cuda:0")  # noqa: E731
+        out = [new(nb) for _ in range(6)]
+        pf.pf_injections_elementwise(G, vm, va, out[0], out[1])
+        pf.pf_injections_ybus(G, vm, va, out[2], out[3])
+        pf.pf_injections_vjp(G, vm, va, lp, lq, out[4], out[5])
+        for method in METHODS:
+            out += [new(nb), new(nb), new(G.nnz_j)]
+            pf.pf_jacobian_values(G, method, vm, va, *out[-3:])
+        for layout, buf in zip((pf.PF_PHASOR_SPLIT, pf.PF_PHASOR_INTERLEAVED), ph):
+            out += [new(nb), new(nb), new(G.nnz_j)]
+            pf.pf_ybus_from_phasors(G, layout, nstate, buf, *out[-3:])
+        torch.cuda.synchronize()
+        want = want or out
+        assert all(torch.equal(a, b) for a, b in zip(out, want)), (spb, order)
+
+
 # States below, at and past a thread's four; positions outside the target are
 # skipped and entries that J does not cover stay as they are.
 @pytest.mark.parametrize("nb,nstate", [(3, 1), (40, 4), (41, 5), (700, 3), (701, 13)])

@@ -4,7 +4,10 @@ from __future__ import annotations
 
 import pytest
 
+import numpy as np
+
 from paper_2302_10736_amd import gridgen, pf
+from tests import _grids
 
 CALLS = [(pf.PF_OP_INJECTIONS, pf.PF_METHOD_ELEMENTWISE), (pf.PF_OP_INJECTIONS, pf.PF_METHOD_YBUS),
          (pf.PF_OP_JACOBIAN, pf.PF_METHOD_ELEMENTWISE), (pf.PF_OP_JACOBIAN, pf.PF_METHOD_YBUS),
@@ -31,6 +34,38 @@ def test_launches_below_two_to_the_32_threads(nb, nl, tile):
                 spb, _, _, blocks, threads = _plan(G, call, nstate)
                 assert threads == tile and 1 <= spb <= nstate
                 assert blocks * threads < 1 << 32, (order, call, nstate, spb, blocks)
+
+
+# One long row leaves the other tiles' launch as it is; it only gets work items
+# of its own, in front.
+@pytest.mark.parametrize("nb,deg,tile", [(60_000, 513, 256), (60_000, 3_000, 256), (30_000, 140, 64)])
+@pytest.mark.parametrize("nstate", [2, 7, 32, 128])
+def test_a_long_row_leaves_the_other_tiles_launch(nb, deg, tile, nstate):
+    g = gridgen.make_grid(nb, nb + nb // 3, 0.15, case=9)
+    far = np.arange(1, deg + 1, dtype=np.int32) * (nb // (deg + 2))
+    cat = lambda a, b: np.concatenate([a, np.full(deg, b)])  # noqa: E731
+    h = gridgen.Grid(nb, g.nl + deg, cat(g.fbus, 0).astype(np.int32), np.concatenate([g.tbus, far]).astype(np.int32),
+                     cat(g.r, 0.01), cat(g.x, 0.1), cat(g.b, 0.02), cat(g.tap, 1.0), cat(g.shift, 0.0), g.gs, g.bs)
+    G, H = (pf.Grid.from_grid(x, host_only=True) for x in (g, h))
+    G.set_schedule(tile)
+    H.set_schedule(tile)
+    for call in CALLS:
+        a, b = _plan(G, call, nstate), _plan(H, call, nstate)
+        assert a[:2] == b[:2] and abs(b[3] - a[3]) <= 0.1 * a[3] + 2 * nstate + 16
+
+
+# Parallel circuits lengthen the element-wise rows, not those of Ybus.
+def test_long_rows_of_each_method():
+    g = _grids.random_small(120, 119, 3)
+    far = np.repeat(np.arange(1, 101, dtype=np.int32), 6)
+    n = len(far)
+    cat = lambda a, b: np.concatenate([a, np.full(n, b)])  # noqa: E731
+    G = pf.Grid.from_grid(gridgen.Grid(g.nb, g.nl + n, cat(g.fbus, 0).astype(np.int32), np.concatenate([g.tbus, far]).astype(np.int32),
+                                       cat(g.r, 0.01), cat(g.x, 0.1), cat(g.b, 0.02), cat(g.tap, 1.0), cat(g.shift, 0.0),
+                                       g.gs, g.bs), host_only=True)
+    G.set_schedule(256, 4, pf.PF_ORDER_TILE_MAJOR)
+    ew, yb = (_plan(G, c, 64)[3] for c in CALLS[:2])
+    assert ew >= 64 + 16 and yb <= 16 * 8  # 600 branch ends: 64 items more; 120 nonzeros a row: none
 
 
 def test_debug_launch_argument_checks():
