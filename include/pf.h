@@ -299,8 +299,8 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *   states_per_block  voltage states one workgroup evaluates in turn, with
  *                     the tile's constants held in registers (>= 1; 0 =
  *                     automatic: at most 4 for Jacobian launches, 8 for
- *                     injections and 16 for the adjoint (32 if its tiles just
- *                     fill the GPU), fewer when they do not fill it; with PF_ORDER_AUTO on grids
+ *                     injections and 16 for the adjoint (more if they fill
+ *                     the GPU exactly once), fewer when they do not fill it; with PF_ORDER_AUTO on grids
  *                     numbered without regard to the network 1 or 2).  Tiles
  *                     with a row of more than 64 terms take one in any case
  *   order             order of the (tile, state chunk) work items over the

@@ -954,6 +954,64 @@ int64_t table_bytes(const pf_grid *g, int kind) {
     return 24 * nt * (int64_t)g->tile_items + 24 * (int64_t)g->nb;
 }
 
+constexpr int64_t kSmallTables = (int64_t)1 << 19;
+
+// Workgroups of a kind that the device holds at once.
+int64_t resident_workgroups(const pf_grid *g, int kind) {
+    int per_cu = pf::resident_blocks_per_cu(kind, g->tile_items, g->has_parallel);
+    if (per_cu <= 0) per_cu = 4;
+    return (int64_t)std::max(g->num_cus, 1) * per_cu;
+}
+
+// Estimated time of nt tiles x nstate states walked spb at a time on a device
+// that holds cap workgroups: workgroups of one length start and end together, in
+// rounds, the last chunk's shorter ones fill what is left.  Unit: a state's time
+// with the device full; a workgroup costs three more to start, and a device that
+// is filled to f takes 0.46 + 0.71 f (at most 1) per state.
+double walk_estimate(int64_t nt, int64_t nstate, int64_t spb, int64_t cap) {
+    auto rate = [cap](double n) { return std::min(1.0, 0.46 + 0.71 * n / (double)cap); };
+    const int64_t whole = nstate / spb * nt, rest = nstate % spb, m = whole % cap, room = cap - m;
+    const double len = (double)spb + 3, last = (double)rest + 3, rounds = (double)(whole / cap) * len;
+    if (rest == 0) return rounds + (m ? len * rate((double)m) : 0);
+    if (nt <= room) return rounds + last * rate((double)(m + nt)) + (m ? (len - last) * rate((double)m) : 0);
+    const double filled = (double)nt * last / (double)room;  // time until the room has done the last chunk
+    if (m && filled <= len) return rounds + filled + (len - filled) * rate((double)m);
+    const int64_t left = m ? (int64_t)(((double)nt * last - (double)room * len) / last) : nt;
+    return rounds + (m ? len : 0) + (double)(left / cap) * last + (left % cap ? last * rate((double)(left % cap)) : 0);
+}
+
+// The adjoint's states per workgroup: 16, or 32, or one round that walks all
+// states in equal parts, if that is estimated to take 5.5 % less.  33k buses x 64
+// states 40.9 us at 16, 35.6 at 22 (one round); 5k x 1000 90 and 74 at 50; 20k x 80
+// 37.4 and 33.1 at 20; 100k x 32 50.9 and 49.8 at 32; 200 grids of 118 buses x 37
+// 25.5 and 29.6 at 19, not taken; 20k x 128 46.4 and 48.6 at 32, not taken.  Longer walks
+// drift apart and lose the L2's reuse (100k x 100 183 us at 32, 189 at 100).
+struct AdjointSplit {
+    int spb;
+    bool one_round;  // tile-major: the grouped order's padded grid would not fit in one round
+};
+
+AdjointSplit adjoint_split(const pf_grid *g, int32_t nstate) {
+    const int64_t nt = (int64_t)g->tiles.size(), padded = (nt + 7) / 8 * 8;
+    const int64_t slots = g->order == PF_ORDER_GROUPED ? padded : nt;
+    const int64_t cap = resident_workgroups(g, pf::K_EW_VJP);
+    const int64_t chunks = std::min<int64_t>(nstate, std::max<int64_t>(1, cap / slots));
+    const int fill = (int)((nstate + chunks - 1) / chunks);
+    const int64_t parts = ((int64_t)nstate + fill - 1) / fill;
+    const bool fits = slots * parts <= cap;
+    if (fill <= 16) return {fill, fits && padded * parts > cap};
+    const bool small = table_bytes(g, pf::K_EW_VJP) < kSmallTables;
+    const int64_t each = small ? slots : padded;
+    double best = 0.945 * walk_estimate(each, nstate, 16, cap);
+    AdjointSplit split{16, false};
+    if (!small && walk_estimate(each, nstate, 32, cap) < best) {
+        best = walk_estimate(each, nstate, 32, cap);
+        split = {32, false};
+    }
+    if (fits && (small || fill <= (parts > 1 ? 64 : 32)) && walk_estimate(slots, nstate, fill, cap) <= best) split = {fill, true};
+    return split;
+}
+
 // Work order of a launch (pf::WO_*).  Automatic: for Jacobian launches
 // grouped (each XCD walks its own eighth of the tiles state by state: their
 // tables stay in its L2 while neighbouring workgroups write neighbouring J
@@ -962,9 +1020,10 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 // (2,383 buses x 250 states, Ybus: 20.4 us state-major, 21.0 grouped);
 // tile-major for injections of few states (the state chunks of one tile run on one XCD, so
 // its tables come from that XCD's L2 after the first chunk) and grouped for
-// the adjoint, whose tables are the heaviest (20k buses x 512 states 227 us
-// tile-major, 207 grouped with 16 states per workgroup; 70k x 37 55.3 and
-// 53.4).  Grids numbered without regard to the network (scattered) take
+// the adjoint, whose tables are the heaviest (20k buses x 512 states 214 us
+// tile-major, 202 grouped with 16 states per workgroup), but tile-major where it
+// fills one round (adjoint_split), which the padded grid of the grouped order would
+// exceed (5k x 1000 74 us, 106 grouped).  Grids numbered without regard to the network (scattered) take
 // state-major throughout: every XCD then works on one state at a time, whose
 // arrays fit in its L2 and serve its gathers, where the other orders gather
 // from the states of all resident workgroups at once (100k buses renumbered at
@@ -985,8 +1044,9 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
         default:
             if (g->scattered) return pf::WO_STATE;
             if (kind == pf::K_EW_S || kind == pf::K_YB_S)
-                return table_bytes(g, kind) >= (int64_t)1 << 19 && (nstate >= 64 || g->ngrids > 1) ? pf::WO_GROUPED : pf::WO_TILE;
-            if (table_bytes(g, kind) >= (int64_t)1 << 19) return pf::WO_GROUPED;
+                return table_bytes(g, kind) >= kSmallTables && (nstate >= 64 || g->ngrids > 1) ? pf::WO_GROUPED : pf::WO_TILE;
+            if (kind == pf::K_EW_VJP && g->states_per_block == 0 && adjoint_split(g, nstate).one_round) return pf::WO_TILE;
+            if (table_bytes(g, kind) >= kSmallTables) return pf::WO_GROUPED;
             return is_jacobian(kind) ? pf::WO_STATE : pf::WO_TILE;
     }
 }
@@ -1002,8 +1062,7 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
 // most 8 for injections (small per-state outputs, so reusing the constants
 // pays); fewer when the tiles alone would leave part of one round of
 // resident workgroups empty (it then splits each tile's states into about
-// resident capacity / tiles chunks).  The adjoint takes that split up to 16
-// states: its record constants (both ends' couplings) are the heaviest.  On
+// resident capacity / tiles chunks).  The adjoint: see adjoint_split.  On
 // scattered grids the states have to stay in step (see work_order): one state
 // per workgroup, two for Jacobian launches whose tables do not stay in L2
 // (S+J of 60k buses x 40 states 96 us at one, 84 at two; 6k x 60: 13.2, 14.7).
@@ -1018,10 +1077,8 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     const int least = (int)std::min<int64_t>(nstate, (slots * nstate + (1 << 22) - 1) >> 22);
     if (g->scattered && g->order == PF_ORDER_AUTO)
         return std::max(least, is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1);
-    int per_cu = pf::resident_blocks_per_cu(kind, g->tile_items, g->has_parallel);
-    if (per_cu <= 0) per_cu = 4;
-    const int64_t capacity = (int64_t)std::max(g->num_cus, 1) * per_cu;
-    int64_t chunks = std::max<int64_t>(1, capacity / nt);
+    if (kind == pf::K_EW_VJP) return std::max(least, adjoint_split(g, nstate).spb);
+    int64_t chunks = std::max<int64_t>(1, resident_workgroups(g, kind) / nt);
     chunks = std::min<int64_t>(chunks, nstate);
     const int fill = (int)((nstate + chunks - 1) / chunks);
     if (is_jacobian(kind)) {
@@ -1033,14 +1090,6 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
         int64_t tb = table_bytes(g, kind);
         if (work_order(g, kind, nstate) == pf::WO_GROUPED) tb /= 8;
         return std::max(least, std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4));
-    }
-    if (kind == pf::K_EW_VJP) {
-        // Where one workgroup per tile fills the chip (seven eighths of it) it
-        // walks up to 32 states, the heaviest tables read once (100k buses x
-        // 32: 50.0 us at 16, 48.6 at 32); else shorter ones even out the rounds
-        // (82k x 20: 28.6 at 16, 32.2 at 20; 14k x 300: 83 at 16, 93 at 32).
-        const bool full = nt <= capacity && 8 * nt >= 7 * capacity;
-        return std::max(least, std::min(fill, full ? 32 : 16));
     }
     return std::max(least, std::min(fill, 8));
 }

@@ -54,6 +54,21 @@ def test_a_long_row_leaves_the_other_tiles_launch(nb, deg, tile, nstate):
         assert a[:2] == b[:2] and abs(b[3] - a[3]) <= 0.1 * a[3] + 2 * nstate + 16
 
 
+# The adjoint's split over a device of 1,024 resident workgroups: one round of
+# equal walks where that is the shortest at any number of tiles (tile-major, never
+# a workgroup more than the device holds), else 16 or 32 states per workgroup.
+@pytest.mark.parametrize("nb,nstate,want", [(5_000, 1_000, 50), (5_000, 2_000, 100), (33_000, 64, 22), (33_000, 48, 16),
+                                            (50_000, 40, 20), (96_500, 32, 32), (100_000, 32, 32), (105_000, 32, 16),
+                                            (70_000, 37, 16), (20_000, 80, 20), (20_000, 128, 16), (20_000, 40, 10),
+                                            (100_000, 100, 32), (100_000, 20, 20), (60_000, 20, 16)])
+def test_adjoint_split(nb, nstate, want):
+    G = pf.Grid.from_grid(gridgen.make_grid(nb, int(1.3 * nb), 0.15, case=9), host_only=True)
+    spb, order, _, blocks, _ = _plan(G, CALLS[6], nstate)
+    assert spb == want
+    if order == pf.PF_ORDER_TILE_MAJOR:
+        assert blocks <= 1_024 + 7
+
+
 # Parallel circuits lengthen the element-wise rows, not those of Ybus.
 def test_long_rows_of_each_method():
     g = _grids.random_small(120, 119, 3)
