@@ -315,8 +315,8 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     (Jacobian launches and the adjoint: grouped, below
  *                     512 KB of tile tables state-major and tile-major;
  *                     injections: tile-major, so the state chunks of one
- *                     tile share an L2, or grouped for many states or
- *                     grids; all of them state-major on grids numbered
+ *                     tile share an L2, or grouped for many states of
+ *                     large grids; all of them state-major on grids numbered
  *                     without regard to the network)
  * The initial schedule is tile_items 256 (with several grids per handle:
  * the smallest of 64, 128, 256 that holds the mean branch ends per grid,

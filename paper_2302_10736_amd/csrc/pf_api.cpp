@@ -956,6 +956,8 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 
 constexpr int64_t kSmallTables = (int64_t)1 << 19;
 
+int64_t input_bytes(const pf_grid *g, int32_t nstate) { return 16 * (int64_t)g->nb * nstate; }
+
 // Workgroups of a kind that the device holds at once.
 int64_t resident_workgroups(const pf_grid *g, int kind) {
     int per_cu = pf::resident_blocks_per_cu(kind, g->tile_items, g->has_parallel);
@@ -1030,9 +1032,11 @@ AdjointSplit adjoint_split(const pf_grid *g, int32_t nstate) {
 // random, injections of 100 states: tile-major 924 us, grouped 577,
 // state-major with 8 states per workgroup 586, with one 315; adjoint of 60k x
 // 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).
-// Injections of many states or grids are grouped too (100k x 128 163 us
-// tile-major, 154 grouped; 43 grids of 728 to 4,838 buses x 70 200 and 162), of
-// fewer not (60k x 40 27.2 and 28.3).
+// Injections of 64 states and more whose inputs take 48 MB are grouped too: up to
+// 5 % less from memory, the same from cache (100k x 128 163 and 155 us, in cache 128
+// and 126; 43 grids of 728 to 4,838 buses x 64 88 and 83, 65 and 66).  Fewer states of
+// one grid or several gain nothing; neither do grids smaller than a tile, whose
+// tiles share no buses (200 grids of 118 buses x 256 83 and 87 in cache).
 int work_order(const pf_grid *g, int kind, int32_t nstate) {
     switch (g->order) {
         case PF_ORDER_TILE_MAJOR:
@@ -1044,7 +1048,10 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
         default:
             if (g->scattered) return pf::WO_STATE;
             if (kind == pf::K_EW_S || kind == pf::K_YB_S)
-                return table_bytes(g, kind) >= kSmallTables && (nstate >= 64 || g->ngrids > 1) ? pf::WO_GROUPED : pf::WO_TILE;
+                return table_bytes(g, kind) >= kSmallTables && nstate >= 64 && input_bytes(g, nstate) >= (int64_t)48 << 20 &&
+                               g->nb >= (int64_t)g->ngrids * g->tile_items
+                           ? pf::WO_GROUPED
+                           : pf::WO_TILE;
             if (kind == pf::K_EW_VJP && g->states_per_block == 0 && adjoint_split(g, nstate).one_round) return pf::WO_TILE;
             if (table_bytes(g, kind) >= kSmallTables) return pf::WO_GROUPED;
             return is_jacobian(kind) ? pf::WO_STATE : pf::WO_TILE;
@@ -1107,7 +1114,7 @@ int ahead_of(const pf_grid *g, const pf::Launch &L) {
     const int64_t walk = ((int64_t)(yb ? g->ytiles : g->tiles).size() + 7) / 8;  // tiles per XCD and state
     // Inputs that fit in half of the 256 MB memory-side cache may be there, and
     // then reading ahead only costs (100k x 32, 51 MB: 80 us without, 88 with).
-    if ((int64_t)L.nstate * g->nb * 16 < (int64_t)128 << 20) return 0;
+    if (input_bytes(g, L.nstate) < (int64_t)128 << 20) return 0;
     if (walk < 8) return 0;
     const int64_t burst = 8, dist = 256 / walk + 1;  // dist: at most 33
     if (L.nstate < dist + burst) return 0;  // fewer states: nothing to gain (40k buses x 8: 1 % lost)

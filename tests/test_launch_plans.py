@@ -69,6 +69,18 @@ def test_adjoint_split(nb, nstate, want):
         assert blocks <= 1_024 + 7
 
 
+# Injections: tile-major for one grid or several, grouped from 64 states and 48 MB
+# of grids larger than a tile.
+@pytest.mark.parametrize("nb,grids,nstate,want", [(40, 200, 64, pf.PF_ORDER_TILE_MAJOR), (40, 200, 1_000, pf.PF_ORDER_TILE_MAJOR),
+                                                  (3_000, 20, 4, pf.PF_ORDER_TILE_MAJOR), (3_000, 20, 63, pf.PF_ORDER_TILE_MAJOR),
+                                                  (3_000, 20, 64, pf.PF_ORDER_GROUPED), (60_000, 1, 64, pf.PF_ORDER_GROUPED),
+                                                  (60_000, 1, 63, pf.PF_ORDER_TILE_MAJOR), (40_000, 1, 64, pf.PF_ORDER_TILE_MAJOR)])
+def test_order_of_injections(nb, grids, nstate, want):
+    big, bo, ro = gridgen.concat([gridgen.make_grid(nb, int(1.3 * nb), 0.15, case=9, grid=k) for k in range(grids)])
+    G = pf.Grid.from_grid(big, *((bo, ro) if grids > 1 else (None, None)), host_only=True)
+    assert all(_plan(G, call, nstate)[1] == want for call in CALLS[:2])
+
+
 # Parallel circuits lengthen the element-wise rows, not those of Ybus.
 def test_long_rows_of_each_method():
     g = _grids.random_small(120, 119, 3)
