@@ -1014,6 +1014,25 @@ AdjointSplit adjoint_split(const pf_grid *g, int32_t nstate) {
     return split;
 }
 
+// Jacobian launches of scattered grids (see work_order): order, and one or two
+// states per workgroup.  Two, which read the tile tables half as often, pay for
+// tables that do not stay in L2, from 8 states on, and while the arrays of two
+// states stay there (60k buses x 24 S+J 59.5 us at one, 53.6 at two; 60k x 3 10.4,
+// 11.5; 200k x 24 210, 313).  Few states in CSC order, which read more tables per
+// state, are grouped while their arrays take half the L2 (60k x 3, Ybus 13.1 us
+// state-major, 11.1 grouped; 100k x 3 19.2, 20.3).
+struct ScatteredPlan {
+    int spb, order;
+};
+
+ScatteredPlan scattered_plan(const pf_grid *g, int kind, int32_t nstate) {
+    const bool csc = kind == pf::K_EW_SJ_CSC || kind == pf::K_YB_SJ_CSC;
+    const int64_t two = 32 * (int64_t)g->nb;
+    if (!is_jacobian(kind) || table_bytes(g, kind) <= (int64_t)2 << 20) return {1, pf::WO_STATE};
+    if (nstate < 8) return {1, csc && two <= (int64_t)2 << 20 ? pf::WO_GROUPED : pf::WO_STATE};
+    return {two <= (int64_t)4 << 20 ? 2 : 1, pf::WO_STATE};
+}
+
 // Work order of a launch (pf::WO_*).  Automatic: for Jacobian launches
 // grouped (each XCD walks its own eighth of the tiles state by state: their
 // tables stay in its L2 while neighbouring workgroups write neighbouring J
@@ -1046,7 +1065,7 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
         case PF_ORDER_GROUPED:
             return pf::WO_GROUPED;
         default:
-            if (g->scattered) return pf::WO_STATE;
+            if (g->scattered) return scattered_plan(g, kind, nstate).order;
             if (kind == pf::K_EW_S || kind == pf::K_YB_S)
                 return table_bytes(g, kind) >= kSmallTables && nstate >= 64 && input_bytes(g, nstate) >= (int64_t)48 << 20 &&
                                g->nb >= (int64_t)g->ngrids * g->tile_items
@@ -1071,8 +1090,7 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
 // resident workgroups empty (it then splits each tile's states into about
 // resident capacity / tiles chunks).  The adjoint: see adjoint_split.  On
 // scattered grids the states have to stay in step (see work_order): one state
-// per workgroup, two for Jacobian launches whose tables do not stay in L2
-// (S+J of 60k buses x 40 states 96 us at one, 84 at two; 6k x 60: 13.2, 14.7).
+// per workgroup, or two (scattered_plan).
 int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (g->states_per_block > 0) return std::min<int32_t>(g->states_per_block, std::max(nstate, 1));
     if (nstate <= 1) return 1;
@@ -1082,8 +1100,7 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     // grouped order has one for every tile of eight equal shares.
     const int64_t slots = work_order(g, kind, nstate) == pf::WO_GROUPED ? (nt + 7) / 8 * 8 : nt;
     const int least = (int)std::min<int64_t>(nstate, (slots * nstate + (1 << 22) - 1) >> 22);
-    if (g->scattered && g->order == PF_ORDER_AUTO)
-        return std::max(least, is_jacobian(kind) && table_bytes(g, kind) > ((int64_t)2 << 20) ? 2 : 1);
+    if (g->scattered && g->order == PF_ORDER_AUTO) return std::max(least, scattered_plan(g, kind, nstate).spb);
     if (kind == pf::K_EW_VJP) return std::max(least, adjoint_split(g, nstate).spb);
     int64_t chunks = std::max<int64_t>(1, resident_workgroups(g, kind) / nt);
     chunks = std::min<int64_t>(chunks, nstate);

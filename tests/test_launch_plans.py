@@ -81,6 +81,17 @@ def test_order_of_injections(nb, grids, nstate, want):
     assert all(_plan(G, call, nstate)[1] == want for call in CALLS[:2])
 
 
+# Jacobian launches of grids numbered at random: two states per workgroup from 8
+# states on while the arrays of two stay in L2, never an uneven rest of few states.
+@pytest.mark.parametrize("nb,nstate,csr,csc", [(60_000, 3, (1, 2), (1, 3)), (60_000, 7, (1, 2), (1, 3)), (60_000, 8, (2, 2), (2, 2)),
+                                               (100_000, 3, (1, 2), (1, 2)), (100_000, 8, (2, 2), (2, 2)), (10_000, 24, (1, 2), (1, 2)),
+                                               (140_000, 24, (1, 2), (1, 2))])
+def test_scattered_jacobian_plans(nb, nstate, csr, csc):
+    G = pf.Grid.from_grid(gridgen.relabel(gridgen.make_grid(nb, int(1.3 * nb), 0.15, case=9), 9, 1)[0], host_only=True)
+    for call, want in zip(CALLS[2:6], (csr, csr, csc, csc)):
+        assert _plan(G, call, nstate)[:2] == want
+
+
 # Parallel circuits lengthen the element-wise rows, not those of Ybus.
 def test_long_rows_of_each_method():
     g = _grids.random_small(120, 119, 3)
