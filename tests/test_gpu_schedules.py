@@ -51,6 +51,52 @@ def test_read_ahead_same_bits(tile, nb, nstate):
         assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
+def _twins(g, every):
+    """The grid with every ``every``-th branch doubled."""
+    cat = lambda x: np.concatenate([x, x[::every]])  # noqa: E731
+    return gridgen.Grid(g.nb, len(cat(g.fbus)), *[cat(x) for x in (g.fbus, g.tbus, g.r, g.x, g.b, g.tap, g.shift)], g.gs, g.bs)
+
+
+# Launches that read ahead (one has a hub bus, whose row's items of their own take
+# its place) against the plain one-state launch: tile sizes, parallel circuits,
+# several grids, bursts of 4 (from 96 tiles per XCD) and 8, whole and cut ones.
+@pytest.mark.parametrize("tile,nb,grids,nstate,kind", [(256, 60_013, 1, 143, ""), (128, 41_002, 1, 207, ""), (256, 40_001, 1, 211, "twins"),
+                                                       (512, 50_003, 1, 170, "twins"), (256, 20_005, 3, 141, ""), (64, 30_001, 1, 285, ""),
+                                                       (256, 82_001, 1, 105, ""), (256, 50_007, 1, 170, "hub")])
+def test_read_ahead_launches_same_bits(tile, nb, grids, nstate, kind):
+    import torch
+    _gpu.require_gpu()
+    parts = [gridgen.make_grid(nb, nb + nb // 9, 0.15, case=9, grid=k) for k in range(grids)]
+    if kind == "twins":
+        parts = [_twins(parts[0], 13)]
+    if kind == "hub":
+        far = np.arange(1, 701, dtype=np.int32) * 31
+        cat = lambda a, b: np.concatenate([a, np.full(700, b)])  # noqa: E731
+        g = parts[0]
+        parts = [gridgen.Grid(nb, g.nl + 700, cat(g.fbus, 0).astype(np.int32), np.concatenate([g.tbus, far]), cat(g.r, 0.01),
+                              cat(g.x, 0.1), cat(g.b, 0.02), cat(g.tap, 1.0), cat(g.shift, 0.0), g.gs, g.bs)]
+    big, bo, ro = gridgen.concat(parts)
+    G = pf.Grid.from_grid(big, *((bo, ro) if grids > 1 else (None, None)))
+    pf.pf_ybus(G)
+    gen = torch.Generator(device="cuda:0").manual_seed(nstate)
+    vm, va = _shifted((nstate, G.nb)), _shifted((nstate, G.nb))
+    vm.uniform_(0.95, 1.05, generator=gen)
+    va.normal_(0.0, 0.2, generator=gen)
+    p, q = _shifted((nstate, G.nb)), _shifted((nstate, G.nb))
+    j = torch.empty((nstate, G.nnz_j), dtype=torch.float64, device="cuda:0")
+    for method in METHODS:
+        got = []
+        for order, ahead in ((pf.PF_ORDER_AUTO, kind != "hub"), (pf.PF_ORDER_TILE_MAJOR, False)):
+            G.set_schedule(tile, 1, order)
+            assert pf.pf_debug_launch(G, pf.PF_OP_JACOBIAN, method, nstate)[2] == ahead
+            for t in (p, q, j):
+                t.fill_(-7.0)
+            pf.pf_jacobian_values(G, method, vm, va, p, q, j)
+            got.append([t[-20:].clone() for t in (p, q, j)] + [t.view(torch.int64).sum(dim=1) for t in (p, q, j)])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 # Branches below, at and past a wave's 48 outputs and a workgroup's 192, with
 # rows that start at every place of a 128-byte line (nl odd).
 @pytest.mark.parametrize("nl,nstate,off", [(1, 2, 0), (47, 3, 1), (48, 17, 0), (49, 16, 5), (176, 2, 15), (177, 3, 0),
@@ -208,3 +254,9 @@ def test_scatter_states_and_skips(nb, nstate):
     out = torch.full((nstate, out_nnz), -7.0, dtype=torch.float64, device="cuda:0")
     pf.pf_jacobian_scatter(G, _gpu.to_dev(jval), torch.as_tensor(pos, device="cuda:0"), out)
     assert np.array_equal(out.cpu().numpy(), want)
+
+
+# The same above 48 MB of targets, where the stores are streaming ones.
+@pytest.mark.parametrize("nb,nstate", [(12_000, 43), (101_001, 5)])
+def test_scatter_into_large_targets(nb, nstate):
+    test_scatter_states_and_skips(nb, nstate)
