@@ -1118,23 +1118,34 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     return std::max(least, std::min(fill, 8));
 }
 
-// Read-ahead of a launch (read_ahead in pf_kernels.hip): bursts of 8 states,
-// for Jacobian launches of one state per workgroup in the grouped order.
-// Measured on 20k buses x 512 states with the inputs in HBM: no read-ahead
-// 385 us, bursts of 4 states 334, of 8 308, of 16 314-324, of 32 326.  The
-// distance covers the states that one round of workgroups (7 or 8 on each of
-// an XCD's 32 compute units) has in flight.  The states read ahead have to
-// stay in the XCD's L2 until they are used: 3 of its 4 MB.
+// Read-ahead of a launch (read_ahead in pf_kernels.hip), for Jacobian launches of
+// one state per workgroup in the grouped order that the library has chosen (a
+// caller who sets PF_ORDER_GROUPED gets it plain).  It pays where the inputs come
+// from memory and costs where they are still in the 256 MB memory-side cache, which
+// a launch cannot know; below 128 MB of inputs it is left out.  Times in us from
+// memory (from cache), without read-ahead and with bursts of 4 and 8 states:
+//   20k x 256, 82 MB     204 170 159 (127 128 137)    left out
+//   100k x 64, 102 MB    251 196 194 (165 161 169)    left out
+//   100k x 100, 160 MB   393 303 299 (248 248 258)    4
+//   60k x 140, 134 MB    331 263 249 (205 207 220)    4
+//   170k x 60, 163 MB    404 320 303 (254 258 274)    4
+//   20k x 512, 164 MB    408 339 314 (253 260 277)    8
+//   50k x 256, 205 MB    498 401 377 (312 315 315)    8
+//   20k x 1,000, 320 MB  802 661 629 (781 662 618)    8
+//   CSC  100k x 100      416 323 304 (260 268 264)    8
+//   Ybus 100k x 100      409 348 337 (303 298 300)    8
+// Element-wise CSR launches take bursts of 4 where a state is walked by 72
+// workgroups and more per XCD.  The distance covers the states that one round of
+// workgroups (7 or 8 on each of an XCD's 32 compute units) has in flight.  The states
+// read ahead have to stay in the XCD's L2 until they are used: 3 of its 4 MB.
 int ahead_of(const pf_grid *g, const pf::Launch &L) {
     if (!is_jacobian(L.kind) || L.phasor != pf::PH_FLY || L.states_per_block != 1 || L.order != pf::WO_GROUPED) return 0;
+    if (g->order != PF_ORDER_AUTO || input_bytes(g, L.nstate) < (int64_t)128 << 20) return 0;
     const bool yb = L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
     const int64_t walk = ((int64_t)(yb ? g->ytiles : g->tiles).size() + 7) / 8;  // tiles per XCD and state
-    // Inputs that fit in half of the 256 MB memory-side cache may be there, and
-    // then reading ahead only costs (100k x 32, 51 MB: 80 us without, 88 with).
-    if (input_bytes(g, L.nstate) < (int64_t)128 << 20) return 0;
     if (walk < 8) return 0;
-    const int64_t burst = 8, dist = 256 / walk + 1;  // dist: at most 33
-    if (L.nstate < dist + burst) return 0;  // fewer states: nothing to gain (40k buses x 8: 1 % lost)
+    const int64_t burst = L.kind == pf::K_EW_SJ && walk >= 72 ? 4 : 8, dist = 256 / walk + 1;  // dist: at most 33
+    if (L.nstate < dist + burst) return 0;
     if ((burst + dist) * 2 * (int64_t)g->nb > (int64_t)3 << 20) return 0;  // 16 bytes a bus, an eighth of the buses
     return (int)(burst | dist << 8);
 }

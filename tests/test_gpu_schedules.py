@@ -59,7 +59,7 @@ def _twins(g, every):
 
 # Launches that read ahead (one has a hub bus, whose row's items of their own take
 # its place) against the plain one-state launch: tile sizes, parallel circuits,
-# several grids, bursts of 4 (from 96 tiles per XCD) and 8, whole and cut ones.
+# several grids, bursts of 4 (from 72 tiles per XCD) and 8, whole and cut ones.
 @pytest.mark.parametrize("tile,nb,grids,nstate,kind", [(256, 60_013, 1, 143, ""), (128, 41_002, 1, 207, ""), (256, 40_001, 1, 211, "twins"),
                                                        (512, 50_003, 1, 170, "twins"), (256, 20_005, 3, 141, ""), (64, 30_001, 1, 285, ""),
                                                        (256, 82_001, 1, 105, ""), (256, 50_007, 1, 170, "hub")])

@@ -92,6 +92,18 @@ def test_scattered_jacobian_plans(nb, nstate, csr, csc):
         assert _plan(G, call, nstate)[:2] == want
 
 
+# Jacobian launches read later states ahead from 128 MB of inputs on, in the
+# library's own order only.
+@pytest.mark.parametrize("nb,nstate,want", [(20_000, 419, 0), (20_000, 420, 1), (60_000, 139, 0), (60_000, 140, 1), (130_000, 65, 1),
+                                            (260_000, 60, 0)])
+def test_read_ahead_plans(nb, nstate, want):
+    G = pf.Grid.from_grid(gridgen.make_grid(nb, int(1.3 * nb), 0.15, case=9), host_only=True)
+    assert all(_plan(G, call, nstate)[2] == want for call in CALLS[2:6])
+    assert all(_plan(G, call, nstate)[2] == 0 for call in CALLS[:2] + CALLS[6:])
+    G.set_schedule(256, 1, pf.PF_ORDER_GROUPED)
+    assert all(_plan(G, call, nstate)[2] == 0 for call in CALLS)
+
+
 # Parallel circuits lengthen the element-wise rows, not those of Ybus.
 def test_long_rows_of_each_method():
     g = _grids.random_small(120, 119, 3)
