@@ -311,7 +311,9 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *                     PF_ORDER_GROUPED (each of the 8 XCDs owns an eighth
  *                     of the tiles and walks them chunk by chunk: the tiles'
  *                     tables stay in its L2 while neighbouring workgroups
- *                     write neighbouring parts of J) or PF_ORDER_AUTO
+ *                     write neighbouring parts of J; set by the caller it
+ *                     never reads ahead, which suits states that are still in
+ *                     the 256 MB memory-side cache) or PF_ORDER_AUTO
  *                     (Jacobian launches and the adjoint: grouped, below
  *                     512 KB of tile tables state-major and tile-major;
  *                     injections: tile-major, so the state chunks of one
@@ -376,12 +378,18 @@ void pf_graph_free(pf_graph *gr);
  *   ncand, cand  int32[3 ncand] host array of (tile_items, states_per_block,
  *           order) triples, or ncand = 0 for the default set: tile_items in
  *           {64, 128, 256, 512} x states_per_block in {0, 1, 2, 4, 8, 16, 32,
- *           64} up to nstate x the three work orders (one state: the four tile
- *           sizes, one state per workgroup)
+ *           64} up to nstate x the three work orders, and the automatic
+ *           schedule at each tile size (one state: the four tile sizes, one
+ *           state per workgroup)
  *   reps    calls per timing in [1, 1000]: each candidate records `reps`
  *           copies of the op in a graph, replays it untimed for 10 ms, then
  *           takes the median of three replays timed by HIP events on a
- *           private stream
+ *           private stream.  Voltage states of 128 to 256 MB, which one set of
+ *           buffers would keep in the memory-side cache, are copied (640 MB in
+ *           all, freed before the call returns; left out if there is no memory
+ *           for them) and the calls take the sets in turn, so that the choice
+ *           holds for states that come from memory; smaller ones are timed in
+ *           the cache, larger ones do not stay there
  *   best    int32[3] out: the chosen triple; best_us (may be NULL): its
  *           device time per call in microseconds; tried (may be NULL): the
  *           number of candidates timed

@@ -151,16 +151,18 @@ def tune(grid: "pf.Grid", op: str, nstate: int, *, cache: Optional[ScheduleCache
     """Time every candidate schedule, keep the fastest on ``grid`` and record
     it in the cache.  Returns {"schedule", "us", "tried", "key"}.  By default
     the library's native tuner (pf_autotune) times the candidates on seeded
-    synthetic states (:func:`synthetic_op`); ``measure(schedule) -> seconds``
+    synthetic states (:func:`synthetic_op`; 128 MB of them and more as they
+    come from memory, fewer as they lie in the cache); ``measure(schedule) -> seconds``
     replaces it (host-side tests)."""
     cache = cache if cache is not None else ScheduleCache()
     device = device if device is not None else _device_name()
     lib = lib if lib is not None else library_id()
     key = problem_key(grid, op, nstate, device, lib)
-    cands = list(cands) if cands is not None else candidates(nstate)
-    if not cands:
-        raise ValueError("no candidate schedules")
-    if measure is None:
+    if cands is not None or measure is not None:
+        cands = list(cands) if cands is not None else candidates(nstate)
+        if not cands:
+            raise ValueError("no candidate schedules")
+    if measure is None:  # cands None: the library's default set, the automatic schedule among it
         best, best_us, tried = pf.pf_autotune(grid, synthetic_op(grid, op, nstate), cands)
     else:
         best, best_t = None, float("inf")

@@ -956,7 +956,10 @@ int64_t table_bytes(const pf_grid *g, int kind) {
 
 constexpr int64_t kSmallTables = (int64_t)1 << 19;
 
+// Voltage states of a launch.  From kFromMemory on, half of the 256 MB memory-side
+// cache, they are taken to come from memory (see ahead_of).
 int64_t input_bytes(const pf_grid *g, int32_t nstate) { return 16 * (int64_t)g->nb * nstate; }
+constexpr int64_t kFromMemory = (int64_t)128 << 20;
 
 // Workgroups of a kind that the device holds at once.
 int64_t resident_workgroups(const pf_grid *g, int kind) {
@@ -1140,7 +1143,7 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
 // read ahead have to stay in the XCD's L2 until they are used: 3 of its 4 MB.
 int ahead_of(const pf_grid *g, const pf::Launch &L) {
     if (!is_jacobian(L.kind) || L.phasor != pf::PH_FLY || L.states_per_block != 1 || L.order != pf::WO_GROUPED) return 0;
-    if (g->order != PF_ORDER_AUTO || input_bytes(g, L.nstate) < (int64_t)128 << 20) return 0;
+    if (g->order != PF_ORDER_AUTO || input_bytes(g, L.nstate) < kFromMemory) return 0;
     const bool yb = L.kind == pf::K_YB_SJ || L.kind == pf::K_YB_SJ_CSC;
     const int64_t walk = ((int64_t)(yb ? g->ytiles : g->tiles).size() + 7) / 8;  // tiles per XCD and state
     if (walk < 8) return 0;
@@ -1583,12 +1586,55 @@ void pf_graph_free(pf_graph *gr) {
 
 namespace {
 
-// Time per call (microseconds) of `op` under the handle's current schedule:
-// a graph of `reps` copies of the op replayed untimed for warm_ms, then the
-// median over `samples` replays timed by HIP events on stream `st`.
-int time_op(const pf_grid *g, const pf_op &op, int32_t reps, hipStream_t st, hipEvent_t e0, hipEvent_t e1,
+// Inputs of the timed calls: the caller's op, and for inputs that a launch takes to
+// come from memory (see ahead_of) but that one set of buffers would keep in the 256
+// MB memory-side cache, the op on copies of them, 640 MB in all.
+struct TunerInputs {
+    std::vector<pf_op> ops;
+    void *copies = nullptr;
+    ~TunerInputs() {
+        if (copies) (void)hipFree(copies);
+    }
+
+    hipError_t fill(const pf_grid *g, const pf_op &op, hipStream_t st) {
+        ops.assign(1, op);
+        const bool vjp = op.op == PF_OP_VJP;
+        const double *in[4] = {op.vm, op.va, op.lam_p, op.lam_q};
+        const int narr = vjp ? 4 : 2;
+        const size_t one = sizeof(double) * (size_t)op.nstate * (size_t)g->nb;
+        const int64_t set = (int64_t)narr * (int64_t)one, nset = set ? ((int64_t)640 << 20) / set + 1 : 1;
+        if (input_bytes(g, op.nstate) < kFromMemory || set >= (int64_t)256 << 20) return hipSuccess;
+        for (int a = 0; a < narr; ++a)
+            if (!in[a]) return hipSuccess;  // the call itself reports it
+        const size_t stride = (one + 255) & ~size_t(255);
+        if (dev_alloc(&copies, stride * (size_t)narr * (size_t)(nset - 1)) != hipSuccess) {
+            copies = nullptr;
+            return hipSuccess;  // no memory for them: the caller's buffers alone
+        }
+        char *at = static_cast<char *>(copies);
+        for (int64_t k = 1; k < nset; ++k) {
+            pf_op o = op;
+            const double **dst[4] = {&o.vm, &o.va, &o.lam_p, &o.lam_q};
+            for (int a = 0; a < narr; ++a, at += stride) {
+                const hipError_t e = hipMemcpyAsync(at, in[a], one, hipMemcpyDeviceToDevice, st);
+                if (e != hipSuccess) return e;
+                *dst[a] = reinterpret_cast<const double *>(at);
+            }
+            ops.push_back(o);
+        }
+        return hipStreamSynchronize(st);
+    }
+};
+
+// Time per call (microseconds) of `in`'s ops in turn under the handle's current
+// schedule: a graph of `reps` of them (rounded up to whole turns) replayed untimed
+// for warm_ms, then the median over `samples` replays timed by HIP events on `st`.
+int time_op(const pf_grid *g, const TunerInputs &in, int32_t reps, hipStream_t st, hipEvent_t e0, hipEvent_t e1,
             double *us) {
-    std::vector<pf_op> ops(reps, op);
+    const size_t turn = in.ops.size();
+    std::vector<pf_op> ops;
+    while (ops.size() < (size_t)reps) ops.insert(ops.end(), in.ops.begin(), in.ops.begin() + turn);
+    reps = (int32_t)ops.size();
     pf_graph *gr = nullptr;
     int rc = pf_graph_create(g, ops.data(), reps, &gr);
     if (rc) return rc;
@@ -1644,6 +1690,7 @@ int pf_autotune(pf_grid *g, const pf_op *op, int32_t ncand, const int32_t *cand,
                     c.insert(c.end(), {t, 1, PF_ORDER_TILE_MAJOR});
                     continue;
                 }
+                c.insert(c.end(), {t, 0, PF_ORDER_AUTO});
                 for (int32_t s : spbs)
                     if (s <= op->nstate)
                         for (int32_t o : {PF_ORDER_TILE_MAJOR, PF_ORDER_STATE_MAJOR, PF_ORDER_GROUPED})
@@ -1660,13 +1707,19 @@ int pf_autotune(pf_grid *g, const pf_op *op, int32_t ncand, const int32_t *cand,
     hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    int rc = e == hipSuccess ? PF_OK : hip_fail(e, "autotuner stream or events");
+    TunerInputs in;
+    try {
+        if (e == hipSuccess) e = in.fill(g, *op, st);
+    } catch (const std::bad_alloc &) {
+        e = hipErrorOutOfMemory;
+    }
+    int rc = e == hipSuccess ? PF_OK : hip_fail(e, "autotuner stream, events or inputs");
     int32_t bi = -1;
     double bt = 0.0;
     for (int32_t k = 0; k < n && rc == PF_OK; ++k) {
         rc = pf_set_schedule(g, c[3 * k], c[3 * k + 1], c[3 * k + 2]);
         double us = 0.0;
-        if (rc == PF_OK) rc = time_op(g, *op, reps, st, e0, e1, &us);
+        if (rc == PF_OK) rc = time_op(g, in, reps, st, e0, e1, &us);
         if (rc == PF_OK && (bi < 0 || us < bt)) {
             bi = k;
             bt = us;

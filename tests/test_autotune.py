@@ -122,3 +122,37 @@ def test_native_tuner_default_and_given_candidates():
         pf.pf_jacobian_values(G, pf.PF_METHOD_ELEMENTWISE, vm, va, p1, q1, j1)
         torch.cuda.synchronize()
         assert torch.equal(j1, j0) and torch.equal(p1, p0)
+
+
+# 164 MB of states: repeated on one set of buffers they stay in the 256 MB
+# memory-side cache, where the state-major order is the faster one; from memory it
+# takes a third longer than the automatic schedule.
+@pytest.mark.gpu
+def test_tuner_times_large_inputs_from_memory():
+    import torch
+    G = pf.Grid.from_grid(gridgen.grid_20k())
+    op = autotune.synthetic_op(G, "jacobian_ew", 512)
+    vm, va = op["vm"].clone(), op["va"].clone()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    state, auto = (256, 1, pf.PF_ORDER_STATE_MAJOR), (256, 0, pf.PF_ORDER_AUTO)
+    best, us, tried = pf.pf_autotune(G, op, [state, auto])
+    assert tried == 2 and best == auto and us > 0
+    t_state, t_auto = (min(pf.pf_autotune(G, op, [c])[1] for _ in range(2)) for c in (state, auto))
+    assert t_state > 1.15 * t_auto  # in the cache about 0.97
+    assert torch.equal(vm, op["vm"]) and torch.equal(va, op["va"])
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= free - (64 << 20)  # the copies are gone
+
+
+# No memory for the copies: the caller's buffers are timed alone.
+@pytest.mark.gpu
+def test_tuner_without_memory_for_copies():
+    G = pf.Grid.from_grid(gridgen.grid_20k())
+    op = autotune.synthetic_op(G, "jacobian_ew", 430)
+    try:
+        pf.pf_debug_fail_allocs(1)
+        best, us, tried = pf.pf_autotune(G, op, [(256, 0, pf.PF_ORDER_AUTO)], reps=1)
+    finally:
+        pf.pf_debug_fail_allocs(0)
+    assert best == (256, 0, pf.PF_ORDER_AUTO) and tried == 1 and us > 0
