@@ -1087,7 +1087,7 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
 // takes at most 4 states per workgroup for Jacobian launches (their time is
 // the J stream: 8 nnzJ bytes per state against a few bytes of constants),
 // 1 when the tables a workgroup's XCD walks stay in its 4 MB L2 between
-// states (an eighth of them in the grouped order, all otherwise), and at
+// states, and at
 // most 8 for injections (small per-state outputs, so reusing the constants
 // pays); fewer when the tiles alone would leave part of one round of
 // resident workgroups empty (it then splits each tile's states into about
@@ -1111,12 +1111,24 @@ int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (is_jacobian(kind)) {
         // One state per workgroup (the single-state kernel) when the tile
         // tables an XCD walks stay in its L2 across states (an eighth of
-        // them in the grouped order); else up to four per read of the tables
-        // (64 grids of 1k to 80k buses x 4 states: 170 us at two, 158 at
-        // four; 300k buses x 16: 153 and 146).
+        // them in the grouped order); else up to four per read of the tables.
+        // Element-wise CSR launches without parallel circuits, whose tables
+        // are the lightest, take two unless four are all or the inputs exceed
+        // the memory-side cache: four lose there what they gain from memory.
+        // From memory (from cache), one, two and four states per workgroup:
+        //   200k x 16                  129 120 116 (83 93 100)      two
+        //   300k x 16                  192 175 168 (141 134 146)    two
+        //   200k x 16, CSC             137 123 118 (95 93 100)      four
+        //   300k x 16, CSC             205 180 171 (202 151 147)    four
+        //   64 grids of 1k to 80k x 4  201 183 174 (169 137 148)    four
+        //   the same x 16              791 718 676 (787 716 675)    four
+        //   300k x 16, Ybus            204 200 184 (159 148 138)    four
+        //   300k x 16, 6 % parallel    199 181 172 (170 145 148)    four
+        const bool light = kind == pf::K_EW_SJ && !g->has_parallel;
+        const int most = light && nstate > 4 && input_bytes(g, nstate) < 2 * kFromMemory ? 2 : 4;
         int64_t tb = table_bytes(g, kind);
         if (work_order(g, kind, nstate) == pf::WO_GROUPED) tb /= 8;
-        return std::max(least, std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : 4));
+        return std::max(least, std::min(fill, tb <= ((int64_t)2 << 20) ? 1 : most));
     }
     return std::max(least, std::min(fill, 8));
 }

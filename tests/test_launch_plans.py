@@ -104,6 +104,15 @@ def test_read_ahead_plans(nb, nstate, want):
     assert all(_plan(G, call, nstate)[2] == 0 for call in CALLS)
 
 
+# S+J of grids whose tables do not stay in L2: two states per workgroup for
+# element-wise CSR launches whose inputs may be in the memory-side cache, else four.
+@pytest.mark.parametrize("nb,nstate,ew,others", [(140_000, 8, 1, 1), (200_000, 8, 2, 4), (300_000, 4, 4, 4), (300_000, 5, 2, 4),
+                                             (300_000, 55, 2, 4), (300_000, 56, 4, 4)])
+def test_states_per_workgroup_with_large_tables(nb, nstate, ew, others):
+    G = pf.Grid.from_grid(gridgen.make_grid(nb, int(1.3 * nb), 0.15, case=9), host_only=True)
+    assert [_plan(G, call, nstate)[0] for call in CALLS[2:6]] == [ew, others, others, others]
+
+
 # Parallel circuits lengthen the element-wise rows, not those of Ybus.
 def test_long_rows_of_each_method():
     g = _grids.random_small(120, 119, 3)
