@@ -306,3 +306,13 @@ def test_debug_alloc_hook_arguments():
         pf.pf_debug_fail_allocs(-1)
     assert e.value.code == pf.PF_EINVAL
     pf.pf_debug_fail_allocs(0)
+
+
+def test_current_stream_without_raw_lookup():
+    """The current stream's handle comes from the public call where torch has
+    no raw lookup, or only half of it."""
+    from types import SimpleNamespace as NS
+    cuda = NS(is_initialized=lambda: True, current_stream=lambda: NS(cuda_stream=1234))
+    assert pf._stream_lookup(NS(cuda=cuda, _C=NS()))() == 1234
+    assert pf._stream_lookup(NS(cuda=cuda, _C=NS(_cuda_getCurrentRawStream=lambda d: d + 7)))() == 1234
+    assert pf._stream_lookup(NS(cuda=cuda, _C=NS(_cuda_getCurrentRawStream=lambda d: d + 7, _cuda_getDevice=lambda: 3)))() == 10
