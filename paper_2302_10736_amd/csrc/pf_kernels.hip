@@ -1790,33 +1790,42 @@ __global__ void k_ca_branch(DevTwoPhase d, int nstate, int64_t nnz_j, const doub
 // once and copies the entry of spb states.  Positions outside the target
 // are skipped, so a wrong map cannot write out of bounds.  Bound by the
 // memory's writes: runs of entries start and end anywhere in a 128-byte line,
-// and the target's other entries lie between them.  So with four states or more
-// (MANY) neighbouring entries stay on one XCD, and for targets of at most 48 MB
-// (PLAIN) the stores are plain: its L2 joins the parts of a line, where
-// streaming stores write each by itself.  40k buses x 8 states (37 MB): 19 us
-// before, 16 plain, 18 streaming; two or eight states per thread 17.  Larger
-// targets would fill the memory-side cache and push the values still to be read
-// out of it (68k x 8, 69 MB: 35 us before, 41 plain, 30 streaming).  A single
-// state is one short round of workgroups: 100k buses x 1, cold, 7.2 us, 9.1 in
-// the XCD order and 10.1 with plain stores too.
-template <bool MANY, bool PLAIN>
+// and the target's other entries lie between them.  Forms:
+//   SC_FEW    fewer than four states: one state per workgroup, one short round of
+//             workgroups (100k buses x 1, cold, 7.2 us; 9.1 in the XCD order and 10.1
+//             with plain stores too).
+//   SC_CACHED targets of at most 48 MB: up to four states per thread, neighbouring
+//             entries on one XCD, plain stores: its L2 joins the parts of a line,
+//             where streaming stores write each by itself.
+//   SC_LARGE  larger targets, which would fill the memory-side cache and push the
+//             values still to be read out of it: streaming stores, state by state;
+//             but waves whose positions lie apart (a CSC target) store plainly, since
+//             each of their streaming stores would be a memory write of 8 bytes.
+// S+J and copy together, one state per thread with streaming stores for all, and now:
+// 40k buses renumbered at random x 8, CSR target of 36 MB, 37.2 and 34.6 us; 100k x 8,
+// CSR target of 90 MB, 81 and 74, CSC target 366 and 201 (streaming in the XCD order 406).
+enum { SC_FEW, SC_CACHED, SC_LARGE };
+
+template <int FORM>
 __global__ void __launch_bounds__(256)
     k_jscatter(int32_t nstate, int32_t spb, int64_t nnz_j, const double *__restrict__ jval,
                const int32_t *__restrict__ map, int64_t out_nnz, double *__restrict__ out) {
     const int nkb = (int)((nnz_j + 255) / 256);
-    const int w = MANY ? work_index(gridDim.x) : (int)blockIdx.x;
-    const int c = MANY ? w / nkb : (int)blockIdx.y;
-    const int64_t k = (int64_t)(MANY ? w - c * nkb : w) * 256 + threadIdx.x;
+    const int w = FORM == SC_CACHED ? work_index(gridDim.x) : (int)blockIdx.x;
+    const int c = FORM == SC_FEW ? (int)blockIdx.y : w / nkb;
+    const int64_t k = (int64_t)(FORM == SC_FEW ? w : w - c * nkb) * 256 + threadIdx.x;
     if (k >= nnz_j) return;
     const int32_t m = map[k];
     if (m < 0 || m >= out_nnz) return;
-    if constexpr (!MANY) {  // one state per workgroup
+    if constexpr (FORM == SC_FEW) {
         st_out(out + (size_t)c * (size_t)out_nnz + m, jval[(size_t)c * (size_t)nnz_j + k]);
         return;
     }
+    const bool plain = FORM == SC_CACHED ||
+                       __builtin_amdgcn_ballot_w64(abs(m - __builtin_amdgcn_readfirstlane(m)) > 256) != 0;
     const int64_t se = min((int64_t)nstate, ((int64_t)c + 1) * spb);
     for (int64_t s = (int64_t)c * spb; s < se; ++s)
-        if constexpr (PLAIN)
+        if (plain)
             out[(size_t)s * (size_t)out_nnz + m] = jval[(size_t)s * (size_t)nnz_j + k];
         else
             st_out(out + (size_t)s * (size_t)out_nnz + m, jval[(size_t)s * (size_t)nnz_j + k]);
@@ -2140,16 +2149,17 @@ hipError_t launch_jscatter(int32_t nstate, int64_t nnz_j, const double *jval, co
     const int64_t nkb = (nnz_j + 255) / 256;
     const int64_t chunks = std::max<int64_t>(1, ((int64_t)1 << 23) / nkb);  // at most: the grid's limit
     const bool many = nstate >= 4;
-    const int32_t spb = (int32_t)std::max<int64_t>(many ? 4 : 1, (nstate + chunks - 1) / chunks);
+    const int32_t even = (nstate + (nstate + 3) / 4 - 1) / ((nstate + 3) / 4);  // at most four, the last not much fewer
+    const int32_t spb = (int32_t)std::max<int64_t>(many ? even : 1, (nstate + chunks - 1) / chunks);
     const int64_t blocks = (nkb * ((nstate + (int64_t)spb - 1) / spb) + kXcds - 1) / kXcds * kXcds;
     const dim3 grid((unsigned)blocks), block(256);
-    if (many && (int64_t)nstate * out_nnz <= ((int64_t)48 << 20) / 8)
-        hipLaunchKernelGGL((k_jscatter<true, true>), grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
-    else if (many)
-        hipLaunchKernelGGL((k_jscatter<true, false>), grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
+    if (!many)
+        hipLaunchKernelGGL(k_jscatter<SC_FEW>, dim3((unsigned)nkb, (unsigned)nstate), block, 0, stream, nstate, spb, nnz_j, jval,
+                           map, out_nnz, out);
+    else if ((int64_t)nstate * out_nnz <= ((int64_t)48 << 20) / 8)
+        hipLaunchKernelGGL(k_jscatter<SC_CACHED>, grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
     else
-        hipLaunchKernelGGL((k_jscatter<false, false>), dim3((unsigned)nkb, (unsigned)nstate), block, 0, stream, nstate, spb,
-                           nnz_j, jval, map, out_nnz, out);
+        hipLaunchKernelGGL(k_jscatter<SC_LARGE>, grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
     return hipGetLastError();
 }
 

@@ -256,7 +256,26 @@ def test_scatter_states_and_skips(nb, nstate):
     assert np.array_equal(out.cpu().numpy(), want)
 
 
-# The same above 48 MB of targets, where the stores are streaming ones.
+# The same above 48 MB of targets, where stores of positions that lie apart are
+# plain ones and others streaming ones.
 @pytest.mark.parametrize("nb,nstate", [(12_000, 43), (101_001, 5)])
-def test_scatter_into_large_targets(nb, nstate):
-    test_scatter_states_and_skips(nb, nstate)
+@pytest.mark.parametrize("apart", [True, False])
+def test_scatter_into_large_targets(nb, nstate, apart):
+    import torch
+    _gpu.require_gpu()
+    G = pf.Grid.from_grid(gridgen.make_grid(nb, int(1.3 * nb), 0.15, case=9, grid=nb))
+    rng = np.random.default_rng(nb)
+    out_nnz = G.nnz_j + G.nnz_j // 12
+    pos = rng.permutation(out_nnz)[:G.nnz_j].astype(np.int32)
+    if not apart:
+        pos.sort()
+        pos[64 * 1_001:64 * 1_002] = pos[64 * 1_001:64 * 1_002][::-1]
+    pos[::11] = -1
+    pos[5::13] = out_nnz
+    pos, jval = torch.as_tensor(pos, device="cuda:0"), torch.randn((nstate, G.nnz_j), dtype=torch.float64, device="cuda:0")
+    want = torch.full((nstate, out_nnz), -7.0, dtype=torch.float64, device="cuda:0")
+    ok = (pos >= 0) & (pos < out_nnz)
+    want[:, pos[ok].long()] = jval[:, ok]
+    out = torch.full((nstate, out_nnz), -7.0, dtype=torch.float64, device="cuda:0")
+    pf.pf_jacobian_scatter(G, jval, pos, out)
+    assert torch.equal(out, want)
