@@ -1798,12 +1798,13 @@ __global__ void k_ca_branch(DevTwoPhase d, int nstate, int64_t nnz_j, const doub
 //             entries on one XCD, plain stores: its L2 joins the parts of a line,
 //             where streaming stores write each by itself.
 //   SC_LARGE  larger targets, which would fill the memory-side cache and push the
-//             values still to be read out of it: streaming stores, state by state;
-//             but waves whose positions lie apart (a CSC target) store plainly, since
-//             each of their streaming stores would be a memory write of 8 bytes.
+//             values still to be read out of it: two states per thread, streaming
+//             stores; but waves whose positions lie apart (a CSC target) store plainly,
+//             since each of their streaming stores would be a memory write of 8 bytes.
 // S+J and copy together, one state per thread with streaming stores for all, and now:
 // 40k buses renumbered at random x 8, CSR target of 36 MB, 37.2 and 34.6 us; 100k x 8,
-// CSR target of 90 MB, 81 and 74, CSC target 366 and 201 (streaming in the XCD order 406).
+// CSR target of 90 MB, 82 and 77, with gaps 84 and 81, CSC target 369 and 177 (four states
+// per thread 75, 88 and 203, one 90, 92 and 159; streaming in the XCD order 77, 89, 405).
 enum { SC_FEW, SC_CACHED, SC_LARGE };
 
 template <int FORM>
@@ -2149,14 +2150,16 @@ hipError_t launch_jscatter(int32_t nstate, int64_t nnz_j, const double *jval, co
     const int64_t nkb = (nnz_j + 255) / 256;
     const int64_t chunks = std::max<int64_t>(1, ((int64_t)1 << 23) / nkb);  // at most: the grid's limit
     const bool many = nstate >= 4;
-    const int32_t even = (nstate + (nstate + 3) / 4 - 1) / ((nstate + 3) / 4);  // at most four, the last not much fewer
-    const int32_t spb = (int32_t)std::max<int64_t>(many ? even : 1, (nstate + chunks - 1) / chunks);
+    const bool large = (int64_t)nstate * out_nnz > ((int64_t)48 << 20) / 8;
+    // At most four states per thread, or two, the last thread's not much fewer.
+    const int32_t most = !many ? 1 : large ? 2 : 4, rounds = (nstate + most - 1) / most;
+    const int32_t spb = (int32_t)std::max<int64_t>((nstate + rounds - 1) / rounds, (nstate + chunks - 1) / chunks);
     const int64_t blocks = (nkb * ((nstate + (int64_t)spb - 1) / spb) + kXcds - 1) / kXcds * kXcds;
     const dim3 grid((unsigned)blocks), block(256);
     if (!many)
         hipLaunchKernelGGL(k_jscatter<SC_FEW>, dim3((unsigned)nkb, (unsigned)nstate), block, 0, stream, nstate, spb, nnz_j, jval,
                            map, out_nnz, out);
-    else if ((int64_t)nstate * out_nnz <= ((int64_t)48 << 20) / 8)
+    else if (!large)
         hipLaunchKernelGGL(k_jscatter<SC_CACHED>, grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
     else
         hipLaunchKernelGGL(k_jscatter<SC_LARGE>, grid, block, 0, stream, nstate, spb, nnz_j, jval, map, out_nnz, out);
