@@ -1606,18 +1606,15 @@ __global__ void k_tp_branch(DevTwoPhase d, const double *__restrict__ vm, const 
 // 20 output rows of nl values each.  Bound by the stores: a row starts at any
 // multiple of 8 bytes, and a wave's 64 values then cover two partial 128-byte
 // lines for every three or four whole ones, each partial line a memory write
-// of its own.  So a wave evaluates 64 branches, the first 16 of them also the
-// last 16 of the wave before, and stores the 48 whose place in the row makes
-// up three whole lines; the workgroups of neighbouring branches run on one
-// XCD.  41,115 branches x 24 states: 51.8 -> 32.1 us (5.3 TB/s; whole lines
-// without the XCD order 46.4, the order alone 52.2, 256-branch workgroups
-// aligned as a whole 44.5, two or three states per lane 34.6 and 35.3).  Rows
-// that all start on a line (BACK = 0) need no overlap.  A single state (MANY =
-// false) is one short round of workgroups, bound by its loads: neither the
-// overlap nor the XCD order pays there (100k buses, 130k branches cold 7.3 us
-// without, 8.9 with the order and precomputed constants), and the constants are
-// derived from the parameters, 16 bytes a branch less to read.
-template <bool WITH_J, int BACK, bool MANY>
+// of its own.  Of several states (MANY) the workgroups of neighbouring branches
+// run on one XCD, and where BACK = 16 a wave evaluates 64 branches, the first
+// 16 of them also the last 16 of the wave before, and stores the 48 whose place
+// in the row makes up three whole lines.  41,115 branches x 24 states:
+// 51.8 -> 32.1 us (5.3 TB/s; whole lines without the XCD order 46.4, the order
+// alone 52.2, 256-branch workgroups aligned as a whole 44.5, two or three states
+// per lane 34.6 and 35.3).  PRE reads the record constants instead of the
+// parameters.  launch_flows says where each form is taken.
+template <bool WITH_J, int BACK, bool MANY, bool PRE>
 __global__ void __launch_bounds__(256)
     k_flows(DevTwoPhase d, int nstate, int nsb, const double *__restrict__ vm, const double *__restrict__ va,
             double *__restrict__ pf, double *__restrict__ qf, double *__restrict__ pt, double *__restrict__ qt,
@@ -1633,9 +1630,9 @@ __global__ void __launch_bounds__(256)
     const int l = min(max(lr, 0), d.nl - 1);
     const int h = d.br_from[l], k = d.br_to[l];
     const size_t n = (size_t)d.nl;
-    const BranchConsts c = load_consts<MANY>(d, l);
+    const BranchConsts c = load_consts<PRE>(d, l);
     const double phi = d.shift[l];
-    for (int s = s0; s < nstate; s += nsb) {
+    for (int s = s0; s < (MANY ? nstate : 1); s += MANY ? nsb : 1) {
         const double *vms = vm + (size_t)s * d.nb, *vas = va + (size_t)s * d.nb;
         EndVals f, t;
         branch_ends(c, phi, vms[h], vas[h], vms[k], vas[k], f, t);
@@ -2105,7 +2102,7 @@ hipError_t launch_copy_add(const DevTwoPhase &d, int32_t nstate, int64_t nnz_j, 
     return hipGetLastError();
 }
 
-template <int BACK, bool MANY>
+template <bool WITH_J, int BACK, bool MANY, bool PRE>
 hipError_t launch_flows_as(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
                            double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
     // One state per workgroup while the launch holds less than 2^32 threads.
@@ -2113,22 +2110,43 @@ hipError_t launch_flows_as(const DevTwoPhase &d, int32_t nstate, const double *v
     const int64_t nlb = ((int64_t)d.nl + BLOCK + BACK - 1) / BLOCK;
     const int nsb = (int)std::min<int64_t>(nstate, std::max<int64_t>(1, ((int64_t)1 << 23) / nlb));
     const dim3 grid((unsigned)((nlb * nsb + kXcds - 1) / kXcds * kXcds));
-    if (jac)
-        hipLaunchKernelGGL((k_flows<true, BACK, MANY>), grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
-    else
-        hipLaunchKernelGGL((k_flows<false, BACK, MANY>), grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt, qt, jac);
+    hipLaunchKernelGGL((k_flows<WITH_J, BACK, MANY, PRE>), grid, dim3(256), 0, stream, d, nstate, nsb, vm, va, pf, qf, pt,
+                       qt, jac);
     return hipGetLastError();
 }
 
+// The form of a launch (us; measured on 30 grids of 118 to 100k buses, 1 to 200 states):
+//   one state      one short round of workgroups, bound by its loads: no XCD order, no
+//                  overlap, constants read (130k branches with partials, cold 7.0; derived
+//                  7.3, in the XCD order 7.4).
+//   constants      with partials read while a grid's records (56 bytes a branch) stay in
+//                  an XCD's 4 MB of L2 next to the states: 27,000 branches x 8 9.2, derived
+//                  9.6; 78,000 x 24 83.2 and 81.0.  Flows alone have little output to
+//                  hide the 16 bytes more behind: read up to 4 MB of output (13,000 x 5
+//                  3.9 and 4.0; 6,500 x 200, 42 MB 20.5 and 19.5; 23,000 x 200 68.9, 62.1).
+//   overlap        a third more lanes and arithmetic.  Four rows (no partials) never pay
+//                  for it (300 grids x 14 buses x 200: 14.2 with, 12.1 without), nor rows
+//                  that all start on a line, nor short launches (186 branches x 200, 6 MB:
+//                  4.7 and 4.1).  It gains from about 12 MB of output on (25 MB of rows of 6,500
+//                  values 8.3 and 8.6, of 100 grids' odd rows 8.6 and 10.5; 58 MB 13.5 and
+//                  17.9); where rows start on half lines, from 48 MB on (27,000 x 8, 35 MB
+//                  10.2 and 9.2; x 16, 69 MB 16.0 and 16.0; x 64 74.5 and 84.8).
 hipError_t launch_flows(const DevTwoPhase &d, int32_t nstate, const double *vm, const double *va, double *pf,
                         double *qf, double *pt, double *qt, double *jac, hipStream_t stream) {
     if (d.nl == 0 || nstate == 0) return hipSuccess;
+    const auto as = [&](auto launch) { return launch(d, nstate, vm, va, pf, qf, pt, qt, jac, stream); };
+    const bool pre = (int64_t)d.nl * 56 <= 3 << 20;
+    if (!jac)
+        return nstate == 1                              ? as(launch_flows_as<false, 0, false, true>)
+               : (int64_t)nstate * d.nl * 32 <= 4 << 20 ? as(launch_flows_as<false, 0, true, true>)
+                                                        : as(launch_flows_as<false, 0, true, false>);
+    if (nstate == 1) return as(launch_flows_as<true, 0, false, true>);
     const uintptr_t at = reinterpret_cast<uintptr_t>(pf) | reinterpret_cast<uintptr_t>(qf) | reinterpret_cast<uintptr_t>(pt) |
-                         reinterpret_cast<uintptr_t>(qt) | reinterpret_cast<uintptr_t>(jac);
-    const bool lines = at % 128 == 0 && d.nl % 16 == 0;  // every row starts on a line
-    if (nstate == 1) return launch_flows_as<0, false>(d, nstate, vm, va, pf, qf, pt, qt, jac, stream);
-    return lines ? launch_flows_as<0, true>(d, nstate, vm, va, pf, qf, pt, qt, jac, stream)
-                 : launch_flows_as<16, true>(d, nstate, vm, va, pf, qf, pt, qt, jac, stream);
+                         reinterpret_cast<uintptr_t>(qt) | reinterpret_cast<uintptr_t>(jac) | (uintptr_t)d.nl * 8;
+    const int64_t bytes = (int64_t)nstate * d.nl * 160;
+    const bool overlap = at % 128 != 0 && bytes >= (at % 64 == 0 ? 48 : 12) << 20;
+    if (overlap) return pre ? as(launch_flows_as<true, 16, true, true>) : as(launch_flows_as<true, 16, true, false>);
+    return pre ? as(launch_flows_as<true, 0, true, true>) : as(launch_flows_as<true, 0, true, false>);
 }
 
 hipError_t launch_phasor(int32_t layout, int64_t n, const double *vm, const double *va, double *ph, hipStream_t stream) {

@@ -127,6 +127,39 @@ def test_flow_rows_any_alignment(nl, nstate, off):
         assert _gpu.rel_err(got[4][s], np.asarray(oracle.branch_flow_jac(g, vm[s], va[s])).reshape(got[4][s].shape)) <= _gpu.TOL
 
 
+# Every form of the launch: rows on whole lines, on half lines (40 states too few
+# for the overlap, 55 enough) and anywhere (14 too few), sizes around a wave's 48 and
+# a workgroup's 192 outputs, and more branches than an XCD's L2 keeps records of.
+# Each state has the bits of its own launch, and nothing is written beside a row.
+@pytest.mark.parametrize("nl,nstate,off", [(1, 79_000, 1), (47, 1_700, 0), (49, 1_630, 5), (177, 450, 3), (193, 420, 15),
+                                           (385, 210, 0), (5_600, 55, 2), (5_608, 40, 0), (5_608, 60, 0), (5_601, 12, 0),
+                                           (24_000, 5, 0), (24_000, 6, 0),
+                                           (60_000, 2, 0), (60_001, 2, 0), (60_001, 1, 1), (60_008, 2, 8), (60_008, 6, 8)])
+def test_flow_forms_same_bits(nl, nstate, off):
+    import torch
+    _gpu.require_gpu()
+    nb = max(2, int(nl / 1.3))
+    g = gridgen.make_grid(nb, max(nl, nb - 1), 0.3, case=9, grid=nl)
+    G = pf.Grid.from_grid(g)
+    few = min(nstate, 7)
+    vm, va = (_gpu.to_dev(x).repeat(nstate // few + 1, 1)[:nstate].contiguous() for x in gridgen.states(nb, few, case=9, grid=nl))
+    pad = 64
+    def out(*shape):
+        n = int(np.prod(shape))
+        whole = torch.full((n + 2 * pad + off,), -7.0, dtype=torch.float64, device="cuda:0")
+        return whole, whole[pad + off:pad + off + n].view(shape)
+    one = [torch.empty((few, nl), dtype=torch.float64, device="cuda:0") for _ in range(4)]
+    one.append(torch.empty((few, 16, nl), dtype=torch.float64, device="cuda:0"))
+    for s in range(few):
+        pf.pf_branch_flows(G, vm[s], va[s], *[o[s] for o in one])
+    for partials in (False, True):
+        outs = [out(nstate, nl) for _ in range(4)] + ([out(nstate, 16, nl)] if partials else [])
+        pf.pf_branch_flows(G, vm, va, *[o for _, o in outs])
+        for (whole, o), w in zip(outs, one):
+            assert (whole[:pad + off] == -7.0).all() and (whole[pad + off + o.numel():] == -7.0).all()
+            assert all(torch.equal(o[s::few], w[s].expand_as(o[s::few])) for s in range(few))
+
+
 # More states than a launch of less than 2^32 threads holds workgroups of 256:
 # every state of a repeating sequence of seven has the flows of its first turn.
 def test_flows_of_many_states():
