@@ -28,9 +28,11 @@
 // NT records: the piece's 16-term chunks are summed in parallel and folded
 // in order by one thread, so its sums keep the packed path's order.  The
 // work items (tile, chunk of states) map to workgroups XCD by XCD in one of
-// three orders (tile-major, state-major, grouped; see work_item).  The
-// baselines further down (the two-phase and copy-add methods, branch flows) use one thread
-// per branch instead.
+// three orders (tile-major, state-major, grouped; see work_item); in launches
+// of several states, tiles with a row of more than 64 terms take one state per
+// workgroup, before all others, since several states of a long row in turn
+// would outlast the rest.  The baselines further down (the two-phase and copy-add
+// methods, branch flows) use one thread per branch instead.
 //
 // Element-wise records
 // --------------------
@@ -1548,7 +1550,8 @@ __global__ void k_branch_consts(DevTwoPhase d, double *__restrict__ bc) {
 
 // Both ends of a branch (from end first) at one state.  The to end's angle
 // tk - th + phi is the exact negative of the from end's, the sine odd and the
-// cosine even bit for bit, so one evaluation serves both.
+// cosine even bit for bit (at equal angles the sine is -0 for one end and +0 for the
+// other, which no sum shows), so one evaluation serves both.
 __device__ __forceinline__ void branch_ends(const BranchConsts &c, double phi, double vh, double th, double vk, double tk,
                                             EndVals &f, EndVals &t) {
     double sn, cs;
@@ -1632,7 +1635,7 @@ __global__ void __launch_bounds__(256)
     const size_t n = (size_t)d.nl;
     const BranchConsts c = load_consts<PRE>(d, l);
     const double phi = d.shift[l];
-    for (int s = s0; s < (MANY ? nstate : 1); s += MANY ? nsb : 1) {
+    for (int s = s0; s < nstate; s += nsb) {
         const double *vms = vm + (size_t)s * d.nb, *vas = va + (size_t)s * d.nb;
         EndVals f, t;
         branch_ends(c, phi, vms[h], vas[h], vms[k], vas[k], f, t);
@@ -2115,10 +2118,11 @@ hipError_t launch_flows_as(const DevTwoPhase &d, int32_t nstate, const double *v
     return hipGetLastError();
 }
 
-// The form of a launch (us; measured on 30 grids of 118 to 100k buses, 1 to 200 states):
+// The form of a launch (us; measured on 13 grids of 118 to 100k buses, 1 to 200 states):
 //   one state      one short round of workgroups, bound by its loads: no XCD order, no
-//                  overlap, constants read (130k branches with partials, cold 7.0; derived
-//                  7.3, in the XCD order 7.4).
+//                  overlap, constants read (130k branches with partials, states and
+//                  records cold, 7.3; derived 7.4, in the XCD order 8.9).  Its loop of
+//                  one pass stays: without it the same launch took 9.8.
 //   constants      with partials read while a grid's records (56 bytes a branch) stay in
 //                  an XCD's 4 MB of L2 next to the states: 27,000 branches x 8 9.2, derived
 //                  9.6; 78,000 x 24 83.2 and 81.0.  Flows alone have little output to
