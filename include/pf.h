@@ -297,29 +297,41 @@ int pf_jacobian_scatter(const pf_grid *g, int32_t nstate, const double *jval, co
  *   tile_items        workgroup size (64, 128, 256 or 512): branch ends per
  *                     element-wise work tile, Ybus nonzeros per Ybus tile
  *   states_per_block  voltage states one workgroup evaluates in turn, with
- *                     the tile's constants held in registers (>= 1; 0 =
- *                     automatic: at most 4 for Jacobian launches, 8 for
- *                     injections and 16 for the adjoint (more if they fill
- *                     the GPU exactly once), fewer when they do not fill it; with PF_ORDER_AUTO on grids
- *                     numbered without regard to the network 1 or 2).  Tiles
- *                     with a row of more than 64 terms take one in any case
- *   order             order of the (tile, state chunk) work items over the
- *                     workgroups: PF_ORDER_TILE_MAJOR (the state chunks of
- *                     one tile are adjacent), PF_ORDER_STATE_MAJOR (the tiles
- *                     of one state chunk are adjacent, so concurrent
- *                     workgroups write neighbouring parts of J),
- *                     PF_ORDER_GROUPED (each of the 8 XCDs owns an eighth
- *                     of the tiles and walks them chunk by chunk: the tiles'
- *                     tables stay in its L2 while neighbouring workgroups
- *                     write neighbouring parts of J; set by the caller it
- *                     never reads ahead, which suits states that are still in
- *                     the 256 MB memory-side cache) or PF_ORDER_AUTO
- *                     (Jacobian launches and the adjoint: grouped, below
- *                     512 KB of tile tables state-major and tile-major;
- *                     injections: tile-major, so the state chunks of one
- *                     tile share an L2, or grouped for many states of
- *                     large grids; all of them state-major on grids numbered
- *                     without regard to the network)
+ *                     the tile's constants held in registers: >= 1, or 0 for
+ *                     the automatic choice.  That is at most 4 for Jacobian
+ *                     launches, 8 for injections and 16 for the adjoint, or
+ *                     for the adjoint 32 or one full round of workgroups
+ *                     where that is estimated to be faster; fewer where the
+ *                     launch would not fill the GPU.  On grids numbered
+ *                     without regard to the network it is 1, or 2 for
+ *                     Jacobian launches (with PF_ORDER_AUTO only).  Tiles
+ *                     with a row of more than 64 terms take one state per
+ *                     workgroup whatever is set
+ *   order             order of the (tile, states) work items over the
+ *                     workgroups:
+ *     PF_ORDER_TILE_MAJOR   the states of one tile are adjacent: they share
+ *                           an L2 copy of the tile's tables
+ *     PF_ORDER_STATE_MAJOR  the tiles of one state are adjacent: concurrent
+ *                           workgroups write neighbouring parts of J
+ *     PF_ORDER_GROUPED      each of the 8 XCDs owns an eighth of the tiles
+ *                           and walks it state by state: the tables stay in
+ *                           its L2 and neighbouring workgroups write
+ *                           neighbouring parts of J.  Set by the caller it
+ *                           reads no states ahead, which suits states that
+ *                           are still in the 256 MB memory-side cache
+ *     PF_ORDER_AUTO         by the call and the grid:
+ *                             Jacobian    grouped (one state per workgroup
+ *                                         and states of 128 MB or more: read
+ *                                         ahead)
+ *                             adjoint     grouped, or tile-major where it
+ *                                         fills one round of workgroups
+ *                             injections  tile-major, or grouped for 64 or
+ *                                         more states of 48 MB or more
+ *                           With less than 512 KB of tile tables Jacobian
+ *                           launches are state-major, the others tile-major;
+ *                           on grids numbered without regard to the network
+ *                           all are state-major, but Jacobian launches of
+ *                           few states in CSC order, which may be grouped
  * The initial schedule is tile_items 256 (with several grids per handle:
  * the smallest of 64, 128, 256 that holds the mean branch ends per grid,
  * since tiles never span grids), states_per_block 0, PF_ORDER_AUTO.

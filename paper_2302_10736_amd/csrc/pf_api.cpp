@@ -1036,29 +1036,25 @@ ScatteredPlan scattered_plan(const pf_grid *g, int kind, int32_t nstate) {
     return {two <= (int64_t)4 << 20 ? 2 : 1, pf::WO_STATE};
 }
 
-// Work order of a launch (pf::WO_*).  Automatic: for Jacobian launches
-// grouped (each XCD walks its own eighth of the tiles state by state: their
-// tables stay in its L2 while neighbouring workgroups write neighbouring J
-// rows, and later states can be read ahead, see ahead_of); state-major for
-// grids of tables below 512 KB, whose eighth would be fewer than eight tiles
-// (2,383 buses x 250 states, Ybus: 20.4 us state-major, 21.0 grouped);
-// tile-major for injections of few states (the state chunks of one tile run on one XCD, so
-// its tables come from that XCD's L2 after the first chunk) and grouped for
-// the adjoint, whose tables are the heaviest (20k buses x 512 states 214 us
-// tile-major, 202 grouped with 16 states per workgroup), but tile-major where it
-// fills one round (adjoint_split), which the padded grid of the grouped order would
-// exceed (5k x 1000 74 us, 106 grouped).  Grids numbered without regard to the network (scattered) take
-// state-major throughout: every XCD then works on one state at a time, whose
-// arrays fit in its L2 and serve its gathers, where the other orders gather
-// from the states of all resident workgroups at once (100k buses renumbered at
-// random, injections of 100 states: tile-major 924 us, grouped 577,
-// state-major with 8 states per workgroup 586, with one 315; adjoint of 60k x
-// 40: 289, 290, 231 and 130; S+J 60k x 40 grouped 105, state-major 84).
-// Injections of 64 states and more whose inputs take 48 MB are grouped too: up to
-// 5 % less from memory, the same from cache (100k x 128 163 and 155 us, in cache 128
-// and 126; 43 grids of 728 to 4,838 buses x 64 88 and 83, 65 and 66).  Fewer states of
-// one grid or several gain nothing; neither do grids smaller than a tile, whose
-// tiles share no buses (200 grids of 118 buses x 256 83 and 87 in cache).
+// Work order of a launch (pf::WO_*).  The automatic choice and why (us):
+//   Jacobian    grouped: an XCD walks its own eighth of the tiles state by state, whose
+//               tables stay in its L2 while neighbouring workgroups write neighbouring
+//               J rows, and later states can be read ahead (ahead_of).  State-major
+//               below 512 KB of tables, where an eighth is fewer than eight tiles (2,383
+//               buses x 250, Ybus, state-major 20.4, grouped 21.0).
+//   adjoint     grouped, its tables are the heaviest (20k x 512 tile-major 214, grouped
+//               202); tile-major below 512 KB, and where it fills one round that the
+//               grouped order's padded grid would exceed (5k x 1000 74, grouped 106).
+//   injections  tile-major: a tile's chunks run on one XCD and share its tables.  Grouped
+//               from 64 states and 48 MB of inputs on: up to 5 % less from memory, the
+//               same from cache (100k x 128 163 and 155, in cache 128 and 126; 43 grids
+//               of 728 to 4,838 buses x 64 88 and 83).  Not for grids smaller than a
+//               tile, whose tiles share no buses (200 grids of 118 x 256 83 and 87).
+//   scattered   (buses numbered without regard to the network) state-major: each XCD
+//               works on one state at a time, whose arrays fit in its L2, where the
+//               other orders gather from the states of all resident workgroups
+//               (injections of 100k x 100 tile-major 924, grouped 577, state-major
+//               315; adjoint 60k x 40 289, 290 and 130).
 int work_order(const pf_grid *g, int kind, int32_t nstate) {
     switch (g->order) {
         case PF_ORDER_TILE_MAJOR:
@@ -1081,19 +1077,13 @@ int work_order(const pf_grid *g, int kind, int32_t nstate) {
 }
 
 // States per workgroup.  A workgroup keeps its tile's record constants in
-// registers and walks its states one after another, so fewer, longer
-// workgroups read the constants fewer times, while more, shorter workgroups
-// keep more of every state's output stream in flight.  The automatic choice
-// takes at most 4 states per workgroup for Jacobian launches (their time is
-// the J stream: 8 nnzJ bytes per state against a few bytes of constants),
-// 1 when the tables a workgroup's XCD walks stay in its 4 MB L2 between
-// states, and at
-// most 8 for injections (small per-state outputs, so reusing the constants
-// pays); fewer when the tiles alone would leave part of one round of
-// resident workgroups empty (it then splits each tile's states into about
-// resident capacity / tiles chunks).  The adjoint: see adjoint_split.  On
-// scattered grids the states have to stay in step (see work_order): one state
-// per workgroup, or two (scattered_plan).
+// registers and walks its states one after another: fewer, longer workgroups
+// read the constants fewer times, more, shorter ones keep more of every state's
+// output stream in flight.  Automatic: at most 4 for Jacobian launches, whose
+// time is the J stream (1, 2 or 4 by the table below), at most 8 for injections,
+// whose outputs are small; fewer where the tiles alone leave part of one round of
+// resident workgroups empty.  The adjoint: adjoint_split.  Scattered grids, where
+// the states have to stay in step: scattered_plan.
 int auto_states_per_block(const pf_grid *g, int kind, int32_t nstate) {
     if (g->states_per_block > 0) return std::min<int32_t>(g->states_per_block, std::max(nstate, 1));
     if (nstate <= 1) return 1;
