@@ -537,7 +537,7 @@ def main():
         cb = abytes + 32 * g.nl  # + the opposite end's coupling, 16 B per branch end (lane table)
         extra["ew_sj_csc"] = {"evals_per_s": K / ev, "avg_launch_us": ev / K * 1e6,
                               "achieved_GBs": abytes / (ev / K) / 1e9, "over_csr_time": (ev / K) / avg_launch,
-                              "kernel": f"k_ew_csc<{tile}, false, true>", "bytes_read_extra": cb - abytes}
+                              "kernel": f"k_ew_csc<{tile}, false, true, 0>", "bytes_read_extra": cb - abytes}
         log(f"element-wise S+J, CSC order: {ev / K * 1e6:.2f} us/launch")
         for d in reps:
             pf.pf_ybus(d["G"])
@@ -549,7 +549,7 @@ def main():
                                   stream=st)
         ev, wall = timed(yb_csc, K, W)
         extra["ybus_sj_csc"] = {"evals_per_s": K / ev, "avg_launch_us": ev / K * 1e6,
-                                "kernel": f"k_ybus_csc<{tile}, true>"}
+                                "kernel": f"k_ybus_csc<{tile}, true, 0>"}
         log(f"Ybus S+J, CSC order: {ev / K * 1e6:.2f} us/launch")
 
     if want("scatter"):
