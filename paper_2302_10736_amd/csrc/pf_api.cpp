@@ -37,18 +37,21 @@ int hip_fail(hipError_t e, const char *what) {
 }
 
 // Every device allocation of the library goes through here, so that a test
-// can make the next n of them fail (pf_debug_fail_allocs).
+// can make the next n of them fail (pf_debug_fail_allocs) as the runtime would.
+// A failure is taken off the runtime's record of the last error: it is reported by
+// the return value, and the check of the next launch would find it there.
 std::atomic<int> g_fail_allocs{0};
 
 hipError_t dev_alloc(void **p, size_t bytes) {
-    int n = g_fail_allocs.load();
-    while (n > 0) {
-        if (g_fail_allocs.compare_exchange_weak(n, n - 1)) {
-            *p = nullptr;
-            return hipErrorOutOfMemory;
-        }
+    bool forced = false;
+    for (int n = g_fail_allocs.load(); n > 0 && !forced;) forced = g_fail_allocs.compare_exchange_weak(n, n - 1);
+    hipError_t e = hipMalloc(p, forced ? (size_t)1 << 62 : bytes);
+    if (forced) e = hipErrorOutOfMemory;
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
     }
-    return hipMalloc(p, bytes);
+    return e;
 }
 
 // Device arrays are carved from one allocation; each array starts on a

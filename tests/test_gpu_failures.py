@@ -102,3 +102,25 @@ def test_failed_schedule_change_keeps_the_launches():
         G.set_schedule(64, 0, pf.PF_ORDER_AUTO)
     pf.pf_debug_fail_allocs(0)
     assert [pf.pf_debug_launch(G, *c) for c in calls] == before
+
+
+def test_tuner_without_memory_for_its_copies():
+    """States of 128 MB are tuned on copies; without memory for them the tuner
+    times the caller's buffers, and no later call reports the failure."""
+    import torch
+    g = gridgen.grid_500()
+    G = pf.Grid.from_grid(g)
+    n = (128 << 20) // (16 * g.nb) + 1
+    vm, va = (to_dev(x).repeat(n, 1) for x in gridgen.states(g.nb, 1, case=0))
+    p, q = torch.empty_like(vm), torch.empty_like(vm)
+    op = dict(op=pf.PF_OP_INJECTIONS, method=pf.PF_METHOD_ELEMENTWISE, vm=vm, va=va, out_a=p, out_b=q)
+    pf.pf_debug_fail_allocs(1)
+    best, us, tried = pf.pf_autotune(G, op, cands=[(256, 0, pf.PF_ORDER_AUTO), (256, 8, pf.PF_ORDER_TILE_MAJOR)], reps=1)
+    assert best in ((256, 0, pf.PF_ORDER_AUTO), (256, 8, pf.PF_ORDER_TILE_MAJOR)) and us > 0 and tried == 2
+    pf.pf_debug_fail_allocs(1)
+    with pytest.raises(pf.PFError) as e:
+        G.set_schedule(128, 3, pf.PF_ORDER_TILE_MAJOR)
+    assert e.value.code == pf.PF_ENOMEM
+    pf.pf_injections_elementwise(G, vm, va, p, q)
+    torch.cuda.synchronize()
+    assert torch.equal(p, p[:1].expand_as(p)) and torch.equal(q, q[:1].expand_as(q))
